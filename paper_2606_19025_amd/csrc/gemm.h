@@ -1,0 +1,160 @@
+// Shared by the grouped-GEMM kernels (bf16: gemm.hip, fp32: gemm_f32.hip): the
+// GEMM kinds, their arguments, the group table and the launch record.
+#pragma once
+#include <type_traits>
+
+#include "common.h"
+
+namespace moe {
+
+// UP_FWD and DH_BWD are GU_FWD and DHH_BWD for the SiLU expert (one first
+// projection W1 [H, d] instead of [Wg; Wu]).
+enum GemmKind {
+  GU_FWD = 0, DOWN_FWD = 1, DHH_BWD = 2, DX_BWD = 3, DWD = 4, DWGU = 5, UP_FWD = 6, DH_BWD = 7
+};
+
+template <int KIND>
+struct Kind {
+  static constexpr bool MRAG = KIND <= DX_BWD || KIND >= UP_FWD;  // ragged in M (else in K)
+  static constexpr bool A_KC = MRAG;                                // A contiguous along k
+  static constexpr bool B_KC = KIND <= DOWN_FWD || KIND == UP_FWD;  // B contiguous along k
+};
+
+struct GemmArgs {
+  const void* A;
+  const void* B;
+  void* C;
+  const void* aux;  // gu, read by the DHH_BWD epilogue
+  void* out2;       // h, written by the GU_FWD epilogue
+  const int32_t* offsets;
+  long lda, ldb, ldc;
+  long b_gs, c_gs;  // per-group strides (elements) of B and C
+  long c_split;     // stride (elements) between the split-K partial outputs
+  int n_groups, cap, M, N, K, H, accumulate;
+  int ksplit;       // K-ragged kinds: each group's rows split in ksplit parts (0 = 1)
+  // DOWN_FWD and DX_BWD (bf16): the kernel may cut K into up to ksplit_max
+  // parts (its choice from the device-side group sizes); part p's fp32
+  // partial goes to part + p c_split ([cap, N] each) and the choice to
+  // *ksplit_used, for splitk_rows_reduce_kernel.  ksplit_max <= 1: no split.
+  int ksplit_max;
+  float* part;
+  int* ksplit_used;
+};
+
+DEVI int clamp_row(int v, int cap) { return v < 0 ? 0 : (v > cap ? cap : v); }
+
+// s_waitcnt immediate (gfx9 family): vmcnt in bits [3:0] and [15:14],
+// expcnt in [6:4], lgkmcnt in [11:8]; a field at its maximum does not wait.
+constexpr int waitcnt_imm(int vm, int lgkm) {
+  return (vm & 15) | (((vm >> 4) & 3) << 14) | (7 << 4) | ((lgkm & 15) << 8);
+}
+#define WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(waitcnt_imm((n), 15))
+#define WAIT_LGKMCNT(n) __builtin_amdgcn_s_waitcnt(waitcnt_imm(63, (n)))
+
+// Wait until at most PER * min(n, MAXN) vector memory operations are
+// outstanding; n <= 0 waits for all of them (n wave-uniform: s_waitcnt takes
+// only an immediate).
+template <int PER, int MAXN>
+DEVI void wait_vm_groups(int n) {
+  if constexpr (MAXN > 0) {
+    if (n >= MAXN) {
+      WAIT_VMCNT(PER * MAXN);
+      return;
+    }
+    wait_vm_groups<PER, MAXN - 1>(n);
+  } else {
+    WAIT_VMCNT(0);
+  }
+}
+
+// Group table of one set, staged in LDS once per block: the group offsets
+// clamped to [0, cap] (c), their running maximum (b: group g of an M-ragged
+// kind is rows [b[g], b[g+1])) and the number of m-tiles before group g (p).
+constexpr int kMaxGroups = 256;
+struct GroupTable {
+  int c[kMaxGroups + 1], b[kMaxGroups + 1], p[kMaxGroups + 1];
+};
+
+DEVI int wave_incl_max(int v) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int u = __shfl_up(v, o, 64);
+    if (lane >= o) v = max(v, u);
+  }
+  return v;
+}
+DEVI int wave_incl_sum(int v) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int u = __shfl_up(v, o, 64);
+    if (lane >= o) v += u;
+  }
+  return v;
+}
+
+// Fill t from set a for m-tiles of BM rows (one wave; n_groups <= kMaxGroups).
+template <int BM>
+DEVI void build_group_table(const GemmArgs& a, GroupTable& t) {
+  const int lane = threadIdx.x & 63;
+  const int ng = a.n_groups;
+  int run = 0;
+  for (int g0 = 0; g0 <= ng; g0 += 64) {
+    const int g = g0 + lane;
+    const int c = g <= ng ? clamp_row(a.offsets[g], a.cap) : 0;
+    int m = wave_incl_max(g <= ng ? c : 0);
+    if (g0 > 0) m = max(m, run);
+    if (g <= ng) {
+      t.c[g] = c;
+      t.b[g] = m;
+    }
+    run = __shfl(m, 63, 64);
+  }
+  WAIT_LGKMCNT(0);  // the wave's own table writes (lanes read their neighbours')
+  int acc = 0;
+  for (int g0 = 0; g0 <= ng; g0 += 64) {
+    const int g = g0 + lane;
+    const int tiles = g < ng ? (t.b[g + 1] - t.b[g] + BM - 1) / BM : 0;
+    const int inc = wave_incl_sum(tiles);
+    if (g <= ng) t.p[g] = acc + inc - tiles;
+    acc += __shfl(inc, 63, 64);
+  }
+}
+
+// Kernel argument of the GEMM kernels: up to kMaxSets sets of groups, each of
+// GEMM kind KA or KB (kind_b[s] != 0), whose tiles share one
+// launch - the routed and the merged shared experts of one kind, and in the
+// backward two independent kinds (dHh with dW_d, dX with dW_gu), so that
+// tiles of different lengths fill the CUs together, keep the CUs out of step
+// (their epilogue stores do not all fall at once) and fill each other's last
+// round.
+constexpr int kMaxSets = 4;
+struct GemmLaunch {
+  GemmArgs s[kMaxSets];
+  int kind_b[kMaxSets];
+  int n_sets;
+  int* counters;  // non-null: per-XCD tile counters (zero at launch) for dynamic dealing
+};
+
+constexpr const char* kGemmNames[] = {"gemm_gu_fwd", "gemm_down_fwd", "gemm_dhh_bwd",
+                                      "gemm_dx_bwd", "gemm_dwd", "gemm_dwgu",
+                                      "gemm_up_fwd", "gemm_dh_bwd"};
+
+template <int KA, int KB>
+const char* gemm_name() {
+  if constexpr (KA == KB) return kGemmNames[KA];
+  else if constexpr (KA == DHH_BWD && KB == DWD) return "gemm_dhh_dwd";
+  else if constexpr (KA == DH_BWD && KB == DWD) return "gemm_dh_dwd";
+  else if constexpr (KA == DX_BWD && KB == DWGU) return "gemm_dx_dwgu";
+  else return "gemm_merged";
+}
+
+// fp32: one launch over sets_a[0..na) of kind ka and sets_b[0..nb) of kind kb
+// (kb == ka with nb = 0: one kind).
+hipError_t run_gemm_f32(int ka, int kb, const GemmArgs* sets_a, int na, const GemmArgs* sets_b,
+                        int nb, hipStream_t s);
+
+int num_cus();
+
+}  // namespace moe

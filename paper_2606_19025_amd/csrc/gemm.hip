@@ -22,93 +22,31 @@
 // global -> LDS DMA (details at gemm_bf16_kernel and Cfg).  One launch
 // covers up to two expert sets (routed and shared experts) of one kind, or
 // in the backward two independent kinds (dHh with dW_d, dX with dW_gu).
-// fp32: a plain 64x64 SIMT tile (4x4 outputs per thread) with the same
-// epilogues; used for fp32 layers.
-#include <type_traits>
-
-#include "common.h"
+// fp32: gemm_f32.hip.
+#include "gemm.h"
 #include "kernels.h"
 #include "timing.h"
 
 namespace moe {
+
+int num_cus() {
+  static int cached[64] = {0};
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+  if (cached[dev] == 0) {
+    int n = 0;
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
+      n = 256;
+    cached[dev] = n;
+  }
+  return cached[dev];
+}
+
 namespace {
-
-// UP_FWD and DH_BWD are GU_FWD and DHH_BWD for the SiLU expert (one first
-// projection W1 [H, d] instead of [Wg; Wu]).
-enum GemmKind {
-  GU_FWD = 0, DOWN_FWD = 1, DHH_BWD = 2, DX_BWD = 3, DWD = 4, DWGU = 5, UP_FWD = 6, DH_BWD = 7
-};
-
-template <int KIND>
-struct Kind {
-  static constexpr bool MRAG = KIND <= DX_BWD || KIND >= UP_FWD;  // ragged in M (else in K)
-  static constexpr bool A_KC = MRAG;                                // A contiguous along k
-  static constexpr bool B_KC = KIND <= DOWN_FWD || KIND == UP_FWD;  // B contiguous along k
-};
-
-struct GemmArgs {
-  const void* A;
-  const void* B;
-  void* C;
-  const void* aux;  // gu, read by the DHH_BWD epilogue
-  void* out2;       // h, written by the GU_FWD epilogue
-  const int32_t* offsets;
-  long lda, ldb, ldc;
-  long b_gs, c_gs;  // per-group strides (elements) of B and C
-  long c_split;     // stride (elements) between the split-K partial outputs
-  int n_groups, cap, M, N, K, H, accumulate;
-  int ksplit;       // K-ragged kinds: each group's rows split in ksplit parts (0 = 1)
-  // DOWN_FWD and DX_BWD (bf16): the kernel may cut K into up to ksplit_max
-  // parts (its choice from the device-side group sizes); part p's fp32
-  // partial goes to part + p c_split ([cap, N] each) and the choice to
-  // *ksplit_used, for splitk_rows_reduce_kernel.  ksplit_max <= 1: no split.
-  int ksplit_max;
-  float* part;
-  int* ksplit_used;
-};
 
 struct Tile {
   int g, row0, rows, m0, n0, split;
 };
-
-DEVI int clamp_row(int v, int cap) { return v < 0 ? 0 : (v > cap ? cap : v); }
-
-// Decode the block's tile.  M-ragged: blockIdx.y enumerates the m-tiles of all
-// groups in order; blocks past the last tile return false.  K-ragged:
-// blockIdx.z is the group, rows = its token count (the K extent).
-template <int BM, int BN, int KIND>
-DEVI bool decode_tile(const GemmArgs& a, Tile& t) {
-  t.n0 = blockIdx.x * BN;
-  if constexpr (Kind<KIND>::MRAG) {
-    int mt = blockIdx.y;
-    int b = clamp_row(a.offsets[0], a.cap);
-    for (int g = 0; g < a.n_groups; ++g) {
-      int e = clamp_row(a.offsets[g + 1], a.cap);
-      if (e < b) e = b;
-      const int tiles = (e - b + BM - 1) / BM;
-      if (mt < tiles) {
-        t.g = g;
-        t.row0 = b + mt * BM;
-        t.rows = min(BM, e - t.row0);
-        t.m0 = 0;
-        t.split = 0;
-        return true;
-      }
-      mt -= tiles;
-      b = e;
-    }
-    return false;
-  } else {
-    t.g = blockIdx.z;
-    t.split = 0;
-    t.m0 = blockIdx.y * BM;
-    const int b = clamp_row(a.offsets[t.g], a.cap);
-    const int e = clamp_row(a.offsets[t.g + 1], a.cap);
-    t.row0 = b;
-    t.rows = e > b ? e - b : 0;
-    return true;
-  }
-}
 
 // GU_FWD: tile column c (within a tile of width BN) -> row of w_gate_up[g].
 // Columns come in blocks of 32: gate h-block, up h-block, gate, up, ... so a
@@ -119,143 +57,6 @@ DEVI int gu_brow(int tile_n, int c, int H, bool& ok) {
   const int h = tile_n * (BN / 2) + (q >> 1) * 32 + (c & 31);
   ok = h < H;
   return (q & 1) * H + h;
-}
-
-DEVI float dsilu_f(float g) {
-  const float s = 1.0f / (1.0f + expf(-g));
-  return s * (1.0f + g * (1.0f - s));
-}
-
-// Epilogue for one accumulator element at (tile row i, tile col j).
-template <int KIND, class T>
-DEVI void epi_store(const GemmArgs& a, const Tile& t, int i, int j, float v) {
-  if constexpr (KIND == DOWN_FWD || KIND == DX_BWD) {
-    const int n = t.n0 + j;
-    if (i < t.rows && n < a.N) static_cast<T*>(a.C)[(size_t)(t.row0 + i) * a.ldc + n] = from_f32<T>(v);
-  } else if constexpr (KIND == DHH_BWD) {
-    const int h = t.n0 + j;
-    if (i < t.rows && h < a.N) {
-      const size_t m = (size_t)(t.row0 + i);
-      const T* gu = static_cast<const T*>(a.aux);
-      const float G = to_f32(gu[m * 2 * a.H + h]);
-      const float U = to_f32(gu[m * 2 * a.H + a.H + h]);
-      T* dgu = static_cast<T*>(a.C);
-      dgu[m * 2 * a.H + h] = from_f32<T>(v * U * dsilu_f(G));
-      dgu[m * 2 * a.H + a.H + h] = from_f32<T>(v * silu_f(G));
-    }
-  } else if constexpr (KIND == UP_FWD) {
-    const int h = t.n0 + j;
-    if (i < t.rows && h < a.N) {
-      const size_t m = (size_t)(t.row0 + i);
-      const T A = from_f32<T>(v);
-      static_cast<T*>(a.C)[m * a.ldc + h] = A;
-      static_cast<T*>(a.out2)[m * a.H + h] = from_f32<T>(silu_f(to_f32(A)));
-    }
-  } else if constexpr (KIND == DH_BWD) {
-    const int h = t.n0 + j;
-    if (i < t.rows && h < a.N) {
-      const size_t m = (size_t)(t.row0 + i);
-      const float A = to_f32(static_cast<const T*>(a.aux)[m * a.H + h]);
-      static_cast<T*>(a.C)[m * a.ldc + h] = from_f32<T>(v * dsilu_f(A));
-    }
-  } else if constexpr (KIND == DWD || KIND == DWGU) {
-    const int m = t.m0 + i, n = t.n0 + j;
-    if (m < a.M && n < a.N) {
-      float* c = static_cast<float*>(a.C) + (size_t)t.g * a.c_gs + (size_t)m * a.ldc + n;
-      *c = a.accumulate ? *c + v : v;
-    }
-  }
-}
-
-// GU_FWD epilogue for the pair (G, U) of hidden unit h at tile row i.
-template <class T>
-DEVI void epi_swiglu(const GemmArgs& a, const Tile& t, int i, int h, float G, float U) {
-  if (i < t.rows && h < a.H) {
-    const size_t m = (size_t)(t.row0 + i);
-    T* gu = static_cast<T*>(a.C);
-    gu[m * 2 * a.H + h] = from_f32<T>(G);
-    gu[m * 2 * a.H + a.H + h] = from_f32<T>(U);
-    static_cast<T*>(a.out2)[m * a.H + h] = from_f32<T>(silu_f(G) * U);
-  }
-}
-
-// ---------------------------------------------------------------------------
-// fp32 SIMT kernel
-
-template <int KIND>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a) {
-  constexpr int BM = 64, BN = 64, BK = 16;
-  __shared__ float As[BK][BM + 4];
-  __shared__ float Bs[BK][BN + 4];
-  Tile tl;
-  if (!decode_tile<BM, BN, KIND>(a, tl)) return;
-  const float* A = static_cast<const float*>(a.A);
-  const float* B = static_cast<const float*>(a.B) + (Kind<KIND>::MRAG ? (size_t)tl.g * a.b_gs : 0);
-  const int Kd = Kind<KIND>::MRAG ? a.K : tl.rows;
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < Kd; k0 += BK) {
-    for (int p = tid; p < BM * BK; p += 256) {
-      int i, kk;
-      if constexpr (Kind<KIND>::A_KC) { i = p / BK; kk = p % BK; } else { kk = p / BM; i = p % BM; }
-      const int k = k0 + kk;
-      float v = 0.f;
-      if (k < Kd) {
-        if constexpr (Kind<KIND>::MRAG) {
-          if (i < tl.rows) v = A[(size_t)(tl.row0 + i) * a.lda + k];
-        } else {
-          if (tl.m0 + i < a.M) v = A[(size_t)(tl.row0 + k) * a.lda + tl.m0 + i];
-        }
-      }
-      As[kk][i] = v;
-    }
-    for (int p = tid; p < BN * BK; p += 256) {
-      int j, kk;
-      if constexpr (Kind<KIND>::B_KC) { j = p / BK; kk = p % BK; } else { kk = p / BN; j = p % BN; }
-      const int k = k0 + kk;
-      float v = 0.f;
-      if (k < Kd) {
-        if constexpr (KIND == GU_FWD) {
-          bool ok;
-          const int br = gu_brow<BN>(blockIdx.x, j, a.H, ok);
-          if (ok) v = B[(size_t)br * a.ldb + k];
-        } else if constexpr (KIND == DOWN_FWD || KIND == UP_FWD) {
-          if (tl.n0 + j < a.N) v = B[(size_t)(tl.n0 + j) * a.ldb + k];
-        } else if constexpr (Kind<KIND>::MRAG) {  // NN
-          if (tl.n0 + j < a.N) v = B[(size_t)k * a.ldb + tl.n0 + j];
-        } else {  // TN
-          if (tl.n0 + j < a.N) v = B[(size_t)(tl.row0 + k) * a.ldb + tl.n0 + j];
-        }
-      }
-      Bs[kk][j] = v;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < BK; ++kk) {
-      float av[4], bv[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) { av[u] = As[kk][ty + 16 * u]; bv[u] = Bs[kk][tx + 16 * u]; }
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) acc[u][v] = fmaf(av[u], bv[v], acc[u][v]);
-    }
-    __syncthreads();
-  }
-  if constexpr (KIND == GU_FWD) {
-    // cols tx, tx+16 are gate units h = blockIdx.x*32 + col; cols +32 their up units
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-      for (int v = 0; v < 2; ++v)
-        epi_swiglu<float>(a, tl, ty + 16 * u, blockIdx.x * (BN / 2) + tx + 16 * v, acc[u][v],
-                          acc[u][v + 2]);
-  } else {
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) epi_store<KIND, float>(a, tl, ty + 16 * u, tx + 16 * v, acc[u][v]);
-  }
 }
 
 // ---------------------------------------------------------------------------
@@ -351,29 +152,6 @@ struct Cfg {
 // set-up turns it into an out-of-range offset (it is never read).
 __device__ const u32x4_t kZero16 = {0u, 0u, 0u, 0u};
 
-// s_waitcnt immediate (gfx9 family): vmcnt in bits [3:0] and [15:14],
-// expcnt in [6:4], lgkmcnt in [11:8]; a field at its maximum does not wait.
-constexpr int waitcnt_imm(int vm, int lgkm) {
-  return (vm & 15) | (((vm >> 4) & 3) << 14) | (7 << 4) | ((lgkm & 15) << 8);
-}
-#define WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(waitcnt_imm((n), 15))
-#define WAIT_LGKMCNT(n) __builtin_amdgcn_s_waitcnt(waitcnt_imm(63, (n)))
-
-// Wait until at most PER * min(n, MAXN) vector memory operations are
-// outstanding; n <= 0 waits for all of them (n wave-uniform: s_waitcnt takes
-// only an immediate).
-template <int PER, int MAXN>
-DEVI void wait_vm_groups(int n) {
-  if constexpr (MAXN > 0) {
-    if (n >= MAXN) {
-      WAIT_VMCNT(PER * MAXN);
-      return;
-    }
-    wait_vm_groups<PER, MAXN - 1>(n);
-  } else {
-    WAIT_VMCNT(0);
-  }
-}
 // 16-byte (b128) or 8-byte store through a buffer resource; an offset at or
 // past the resource's record count is dropped, so every lane issues the
 // store and the count of outstanding vector memory operations is known at
@@ -547,60 +325,6 @@ DEVI float silu_fast(float g) { return g * sigmoid_fast(g); }
 // (32 / GROUP_M) rectangle and share GROUP_M A panels and 32 / GROUP_M B
 // panels in L2.
 
-// Group table of one set, staged in LDS once per block: the group offsets
-// clamped to [0, cap] (c), their running maximum (b: group g of an M-ragged
-// kind is rows [b[g], b[g+1])) and the number of m-tiles before group g (p).
-constexpr int kMaxGroups = 256;
-struct GroupTable {
-  int c[kMaxGroups + 1], b[kMaxGroups + 1], p[kMaxGroups + 1];
-};
-
-DEVI int wave_incl_max(int v) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int u = __shfl_up(v, o, 64);
-    if (lane >= o) v = max(v, u);
-  }
-  return v;
-}
-DEVI int wave_incl_sum(int v) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int u = __shfl_up(v, o, 64);
-    if (lane >= o) v += u;
-  }
-  return v;
-}
-
-// Fill t from set a (one wave; n_groups <= kMaxGroups).
-DEVI void build_group_table(const GemmArgs& a, GroupTable& t) {
-  const int lane = threadIdx.x & 63;
-  const int ng = a.n_groups;
-  int run = 0;
-  for (int g0 = 0; g0 <= ng; g0 += 64) {
-    const int g = g0 + lane;
-    const int c = g <= ng ? clamp_row(a.offsets[g], a.cap) : 0;
-    int m = wave_incl_max(g <= ng ? c : 0);
-    if (g0 > 0) m = max(m, run);
-    if (g <= ng) {
-      t.c[g] = c;
-      t.b[g] = m;
-    }
-    run = __shfl(m, 63, 64);
-  }
-  WAIT_LGKMCNT(0);  // the wave's own table writes (lanes read their neighbours')
-  int acc = 0;
-  for (int g0 = 0; g0 <= ng; g0 += 64) {
-    const int g = g0 + lane;
-    const int tiles = g < ng ? (t.b[g + 1] - t.b[g] + GT - 1) / GT : 0;
-    const int inc = wave_incl_sum(tiles);
-    if (g <= ng) t.p[g] = acc + inc - tiles;
-    acc += __shfl(inc, 63, 64);
-  }
-}
-
 // Output tiles form an m_tiles x n_tiles grid (M-ragged kinds: m-tiles of all
 // groups in group order; K-ragged kinds: (group, split part, m-tile)
 // triples).
@@ -670,21 +394,6 @@ DEVI int col_tiles(const GemmArgs& a) {
   return ((KIND == GU_FWD ? 2 * a.H : a.N) + GT - 1) / GT;
 }
 
-// Kernel argument of the bf16 kernel: up to kMaxSets sets of groups, each of
-// GEMM kind KA or KB (kind_b[s] != 0), whose tiles share one persistent
-// launch - the routed and the merged shared experts of one kind, and in the
-// backward two independent kinds (dHh with dW_d, dX with dW_gu), so that
-// tiles of different lengths fill the CUs together, keep the CUs out of step
-// (their epilogue stores do not all fall at once) and fill each other's last
-// round.
-constexpr int kMaxSets = 4;
-struct GemmLaunch {
-  GemmArgs s[kMaxSets];
-  int kind_b[kMaxSets];
-  int n_sets;
-  int* counters;  // non-null: per-XCD tile counters (zero at launch) for dynamic dealing
-};
-
 template <int K>
 using KindTag = std::integral_constant<int, K>;
 
@@ -731,7 +440,7 @@ __global__ __launch_bounds__(512, 2) void gemm_bf16_kernel(GemmLaunch L) {
   const int per_xcd = gridDim.x / N_XCD;
   const int xcd = blockIdx.x % N_XCD;
   __shared__ GroupTable gtab[kMaxSets];
-  if (wave < L.n_sets) build_group_table(L.s[wave], gtab[wave]);
+  if (wave < L.n_sets) build_group_table<GT>(L.s[wave], gtab[wave]);
   __syncthreads();
   // per set: m-tiles, n-tiles, this XCD's first tile and its reduction
   // length per tile (rows per group for the K-ragged kinds, from the table)
@@ -1330,19 +1039,6 @@ __global__ __launch_bounds__(512, 2) void gemm_bf16_kernel(GemmLaunch L) {
   }
 }
 
-int num_cus() {
-  static int cached[64] = {0};
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-  if (cached[dev] == 0) {
-    int n = 0;
-    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
-      n = 256;
-    cached[dev] = n;
-  }
-  return cached[dev];
-}
-
 template <int KIND>
 long max_tiles(const GemmArgs& a) {
   constexpr int BM = Cfg<KIND>::BM;
@@ -1350,19 +1046,6 @@ long max_tiles(const GemmArgs& a) {
   return Kind<KIND>::MRAG
              ? (ceil_div(a.cap, BM) + (long)a.n_groups) * n_tiles * std::max(1, a.ksplit_max)
              : (long)a.n_groups * std::max(1, a.ksplit) * ceil_div(a.M, BM) * n_tiles;
-}
-
-constexpr const char* kGemmNames[] = {"gemm_gu_fwd", "gemm_down_fwd", "gemm_dhh_bwd",
-                                      "gemm_dx_bwd", "gemm_dwd", "gemm_dwgu",
-                                      "gemm_up_fwd", "gemm_dh_bwd"};
-
-template <int KA, int KB>
-const char* gemm_name() {
-  if constexpr (KA == KB) return kGemmNames[KA];
-  else if constexpr (KA == DHH_BWD && KB == DWD) return "gemm_dhh_dwd";
-  else if constexpr (KA == DH_BWD && KB == DWD) return "gemm_dh_dwd";
-  else if constexpr (KA == DX_BWD && KB == DWGU) return "gemm_dx_dwgu";
-  else return "gemm_merged";
 }
 
 // One bf16 launch over up to kMaxSets sets: sets_a[0..na) of kind KA and
@@ -1395,28 +1078,11 @@ hipError_t run_gemm_bf16(const GemmArgs* sets_a, int na, const GemmArgs* sets_b,
   return hipGetLastError();
 }
 
-// One launch per set group of one GEMM kind (fp32: one SIMT launch per set).
+// One launch per set group of one GEMM kind.
 template <int KIND>
-hipError_t run_gemm(const GemmArgs* sets, int n_sets, int bf16, hipStream_t s,
-                    int* counters = nullptr) {
-  if (bf16) return run_gemm_bf16<KIND, KIND>(sets, n_sets, nullptr, 0, s, counters);
-  for (int i = 0; i < n_sets; ++i) {
-    const GemmArgs& a = sets[i];
-    dim3 grid;
-    grid.x = ceil_div((KIND == GU_FWD) ? 2 * a.H : a.N, 64);
-    if (Kind<KIND>::MRAG) {
-      grid.y = ceil_div(a.cap, 64) + a.n_groups;
-      grid.z = 1;
-    } else {
-      grid.y = ceil_div(a.M, 64);
-      grid.z = a.n_groups;
-    }
-    if (grid.x == 0 || grid.y == 0 || grid.z == 0) continue;
-    MOE_TIMED(kGemmNames[KIND], s, gemm_f32_kernel<KIND><<<grid, 256, 0, s>>>(a));
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+hipError_t run_gemm(const GemmArgs* sets, int n_sets, int bf16, hipStream_t s) {
+  if (bf16) return run_gemm_bf16<KIND, KIND>(sets, n_sets, nullptr, 0, s, nullptr);
+  return run_gemm_f32(KIND, KIND, sets, n_sets, nullptr, 0, s);
 }
 
 // counters[0..n) = 0 (the per-XCD tile counters of the next launches)
@@ -1692,11 +1358,11 @@ hipError_t launch_ffn_bwd_sets(const moe_ffn_set* sets, int n_sets, int bf16, in
   if (bf16 && ws) assign_row_parts(dx, sets, n_sets, bf16, d, rows_ws);
   hipError_t e;
   if (!bf16) {
-    e = silu ? run_gemm<DH_BWD>(hh, n_sets, bf16, s) : run_gemm<DHH_BWD>(hh, n_sets, bf16, s);
+    // the same two launches as bf16
+    e = run_gemm_f32(silu ? DH_BWD : DHH_BWD, DWD, hh, n_sets, wd, n_sets, s);
     if (e != hipSuccess) return e;
-    if ((e = run_gemm<DX_BWD>(dx, n_sets, bf16, s)) != hipSuccess) return e;
-    if ((e = run_gemm<DWD>(wd, n_sets, bf16, s)) != hipSuccess) return e;
-    if ((e = run_gemm<DWGU>(wgu, n_sets, bf16, s)) != hipSuccess) return e;
+    e = run_gemm_f32(DX_BWD, DWGU, dx, n_sets, wgu, n_sets, s);
+    if (e != hipSuccess) return e;
   } else {
     // two launches of two independent kinds each: dHh with dW_d (both read
     // dY), then dX with dW_gu (both read dG/dU); with a workspace their tiles
