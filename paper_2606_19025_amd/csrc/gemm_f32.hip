@@ -6,19 +6,22 @@
 // stages of 32 k, filled by 16-byte global -> LDS DMA NS - 1 k-steps ahead:
 // with registers between global memory and LDS, a k-step of a small GEMM (a
 // few tiles, nothing else on the CU) waited out a whole memory latency.
-// fp32 MFMA runs at 256 flop per clock and CU, so the LDS reads (8 to 16 bytes
-// per clock and wave) and the L2 traffic of 64 x 64 tiles are far below their
-// limits; the tile size is chosen for the number of blocks alone (run_kinds).
+// fp32 MFMA runs at 256 flop per clock and CU, so LDS reads and L2 traffic are
+// far below their limits; the tile size is chosen for the number of blocks
+// (run_kinds).  What is left is the issue of the MFMAs: 70 % of their cycles
+// are busy at 4096 rows, d = 1024, H = 1408 (forward and backward 0.98 ms, 108
+// TFLOP/s; the 64 x 64 SIMT tiles before: about 14 TFLOP/s).
 //
-// Out-of-range rows, columns and k are read from a block of zeros; addresses
-// are 64-bit, so operands may have any size.
+// k past the last are read from a block of zeros.  A piece's address is a 64-bit
+// wave-uniform one plus a lane's 32-bit offset, or 64-bit per lane where that
+// does not reach, so operands may have any size.
 //
 // LDS layouts (per operand and stage), and which index an MFMA lane holds:
 //  k-contiguous: row r holds 32 k (128 bytes); its 16-byte chunk c sits at
 //    position c ^ ((r >> 1) & 7), so the 16 lanes of one read (consecutive
 //    rows, one chunk) hit distinct bank groups.  Lane l reads 4 k of row
 //    l % 16 of a 16-row tile: k = 16 q + 4 (l / 16) + e feeds MFMA e.
-//  m/n-contiguous: row k holds the tile's 32 MI (32 NJ) indices.  Lane l reads
+//  m/n-contiguous: row k holds the tile's 32 MI (or 32 NJ) indices.  Lane l reads
 //    the MI consecutive indices MI (l % 16) + i of row 16 q + 4 (l / 16) + e:
 //    index i belongs to the wave's MFMA tile i.
 // The MFMA takes B as its first operand: register t of tile (i, j) is output
@@ -33,11 +36,20 @@ namespace {
 
 __device__ __attribute__((aligned(16))) const float kZeros[4] = {0.f, 0.f, 0.f, 0.f};
 
-// lane l's 16 bytes at p -> LDS at base + 16 l (base wave-uniform).  The asm
-// sets m0 and leaves the one wait state that an LDS DMA needs after it.
+// A lane's 16 bytes -> LDS at base + 16 lane (base wave-uniform), from p, or from
+// offset off (bytes) of a wave-uniform pointer.  The asm sets m0 and leaves the
+// one wait state that an LDS DMA needs after it.
+DEVI unsigned lds_offset(char* base) {
+  return __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(lds_void_t*)base);
+}
 DEVI void dma16(const float* p, char* base) {
-  const unsigned m0 = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(lds_void_t*)base);
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(p), "s"(m0)
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(p),
+               "s"(lds_offset(base))
+               : "m0", "memory");
+}
+DEVI void dma16(const float* uniform, unsigned off, char* base) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off),
+               "s"(uniform), "s"(lds_offset(base))
                : "m0", "memory");
 }
 
@@ -92,11 +104,11 @@ DEVI void store_cols(const GemmArgs& a, const TileF32& t, int i, int n, f32x4_t 
   }
 }
 
-// Per-lane source of one 16-byte DMA piece: its address at k-step 0, its first
-// k there and the k extent (0 for a row or column past the tile's).
+// What a lane reads in one 16-byte DMA piece of a k-step: 4 floats at row r,
+// column c of the operand's rows there, the first of which is
+// k-step-relative index k.
 struct Piece {
-  const float* p;
-  int k, k_end;
+  int r, c, k;
 };
 
 template <int KIND, int MI, int NJ, int NS>
@@ -117,63 +129,71 @@ DEVI void gemm_f32_tile(const GemmArgs& a, const TileF32& tl, char* lds) {
 
   // row of w_gate_up[g] (or of the second operand) behind tile column c; the
   // gate and up units of GU_FWD alternate in blocks of 8 NJ columns, half of a
-  // wave's, so that a lane holds G and U of the same unit
-  auto b_row = [&](int c, bool& ok) -> size_t {
+  // wave's, so that a lane holds G and U of the same unit.  Columns past the
+  // last (and rows past the group's, below) repeat a valid one: their outputs
+  // are not stored.
+  auto b_row = [&](int c) {
     if constexpr (KIND == GU_FWD) {
       constexpr int HW = 8 * NJ;
       const int h = (n0 >> 1) + (c / (2 * HW)) * HW + c % HW;
-      ok = h < a.H;
-      return (size_t)((c / HW) & 1) * a.H + h;
+      return ((c / HW) & 1) * a.H + (h < a.H ? h : 0);
     } else {
-      ok = n0 + c < a.N;
-      return (size_t)(n0 + c);
+      return min(n0 + c, a.N - 1);
     }
   };
   // piece q of a k-contiguous operand: rows 8 q .. 8 q + 7
-  auto piece_kc = [&](int q, const float* base, long ld, auto&& row_of) {
+  auto piece_kc = [&](int q, auto&& row_of) {
     const int r = q * 8 + (lane >> 3);
-    const int c = (lane & 7) ^ ((r >> 1) & 7);
-    bool ok;
-    const size_t row = row_of(r, ok);
-    return Piece{base + (ok ? row * ld : 0) + c * 4, c * 4, ok ? Kd : 0};
+    const int c = ((lane & 7) ^ ((r >> 1) & 7)) * 4;
+    return Piece{row_of(r), c, c};
   };
   // piece q of an m/n-contiguous operand of R indices per row: 256 / R rows
-  auto piece_mn = [&](int q, const float* base, long ld, int R, int i0, int end) {
+  auto piece_mn = [&](int q, int R, int i0, int end) {
     const int k = q * (256 / R) + lane / (R / 4);
     const int i = i0 + lane % (R / 4) * 4;
-    return Piece{base + (size_t)k * ld + (i < end ? i : 0), k, i < end ? Kd : 0};
+    return Piece{k, i < end ? i : 0, k};
   };
-  Piece pa[MI], pb[NJ];
+  // piece x: A's (x < MI), then B's
+  auto piece = [&](int x) {
+    if (x < MI) {
+      const int q = x * 4 + wave;
+      if constexpr (K_::A_KC) return piece_kc(q, [&](int r) { return min(r, tl.rows - 1); });
+      else return piece_mn(q, BM, tl.m0, a.M);
+    }
+    const int q = (x - MI) * 4 + wave;
+    if constexpr (K_::B_KC) return piece_kc(q, b_row);
+    else return piece_mn(q, BN, n0, a.N);
+  };
+  // byte offsets of the lane's pieces; 32 bits unless the operand's rows of one
+  // k-step (an expert's whole weight if k-contiguous) reach over 4 GiB
+  const bool narrow = max(a.lda * BM, a.ldb * (K_::B_KC ? max(BN, a.N) : BN)) < (1L << 30);
+  unsigned off[MI + NJ];
 #pragma unroll
-  for (int i = 0; i < MI; ++i) {
-    const int q = i * 4 + wave;
-    if constexpr (K_::A_KC)
-      pa[i] = piece_kc(q, A, a.lda, [&](int r, bool& ok) -> size_t { ok = r < tl.rows; return r; });
-    else
-      pa[i] = piece_mn(q, A, a.lda, BM, tl.m0, a.M);
-  }
-#pragma unroll
-  for (int j = 0; j < NJ; ++j) {
-    const int q = j * 4 + wave;
-    if constexpr (K_::B_KC) pb[j] = piece_kc(q, B, a.ldb, b_row);
-    else pb[j] = piece_mn(q, B, a.ldb, BN, n0, a.N);
+  for (int x = 0; x < MI + NJ; ++x) {
+    const Piece p = piece(x);
+    off[x] = ((unsigned)p.r * (unsigned)(x < MI ? a.lda : a.ldb) + (unsigned)p.c) * 4u;
   }
   const long a_step = K_::A_KC ? BK : BK * a.lda, b_step = K_::B_KC ? BK : BK * a.ldb;
-  // the next k-step's pieces into stage st (called once per k-step, in order)
-  auto load = [&](int st) {
-    char* la = lds + st * STAGE;
-#pragma unroll
-    for (int i = 0; i < MI; ++i) {
-      dma16(pa[i].k < pa[i].k_end ? pa[i].p : kZeros, la + (i * 4 + wave) * 1024);
-      pa[i].p += a_step;
-      pa[i].k += BK;
+  // the operands at the next k-step to load, and that k-step's first k
+  const float *An = A, *Bn = B;
+  int kn = 0;
+  // piece x of the next k-step into stage st.  The last, partial k-step (and
+  // every one where 32 bits do not reach) takes per-lane addresses, zeros past Kd.
+  auto load = [&](char* st, int x) {
+    char* dst = st + (x < MI ? x * 4 : A_BYTES / 1024 + (x - MI) * 4) * 1024 + wave * 1024;
+    const float* base = x < MI ? An : Bn;
+    if (narrow && kn + BK <= Kd) {
+      dma16(base, off[x], dst);
+    } else {
+      const Piece p = piece(x);
+      const float* src = base + (size_t)p.r * (x < MI ? a.lda : a.ldb) + p.c;
+      dma16(kn + p.k < Kd ? src : kZeros, dst);
     }
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      dma16(pb[j].k < pb[j].k_end ? pb[j].p : kZeros, la + A_BYTES + (j * 4 + wave) * 1024);
-      pb[j].p += b_step;
-      pb[j].k += BK;
-    }
+  };
+  auto advance = [&]() {
+    An += a_step;
+    Bn += b_step;
+    kn += BK;
   };
 
   f32x4_t acc[MI][NJ];
@@ -206,30 +226,72 @@ DEVI void gemm_f32_tile(const GemmArgs& a, const TileF32& tl, char* lds) {
     }
   };
 
+  // both operands' fragments of k-block q of a stage
+  struct Frags {
+    float a[MI][4], b[NJ][4];
+  };
+  auto read = [&](const char* st, int q, Frags& f) {
+    frags(std::bool_constant<K_::A_KC>{}, std::integral_constant<int, MI>{}, st, wm, q, f.a);
+    frags(std::bool_constant<K_::B_KC>{}, std::integral_constant<int, NJ>{}, st + A_BYTES, wn, q, f.b);
+  };
+  // the MFMAs of a k-block; between(e) is issued after the e-th quarter
+  auto mma = [&](const Frags& f, auto&& between) {
 #pragma unroll
-  for (int p = 0; p < NS - 1; ++p)
-    if (p < nk) load(p);
-  for (int kt = 0; kt < nk; ++kt) {
-    // this wave's pieces of k-step kt have landed (later ones may be in
-    // flight); after the barrier everyone's have, and every wave is done with
-    // the stage of k-step kt - 1, which k-step kt + NS - 1 takes
-    wait_vm_groups<MI + NJ, NS - 2>(nk - 1 - kt);
-    __syncthreads();
-    if (kt + NS - 1 < nk) load((kt + NS - 1) % NS);
-    const char* st = lds + (kt % NS) * STAGE;
+    for (int e = 0; e < 4; ++e) {
 #pragma unroll
-    for (int q = 0; q < BK / 16; ++q) {
-      float fa[MI][4], fb[NJ][4];
-      frags(std::bool_constant<K_::A_KC>{}, std::integral_constant<int, MI>{}, st, wm, q, fa);
-      frags(std::bool_constant<K_::B_KC>{}, std::integral_constant<int, NJ>{}, st + A_BYTES, wn, q, fb);
+      for (int i = 0; i < MI; ++i)
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-          for (int j = 0; j < NJ; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[j][e], fa[i][e], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < NJ; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(f.b[j][e], f.a[i][e], acc[i][j], 0, 0, 0);
+      between(e);
+      __builtin_amdgcn_sched_barrier(0);
     }
+  };
+
+#pragma unroll
+  for (int p = 0; p < NS; ++p)
+    if (p < nk) {
+#pragma unroll
+      for (int x = 0; x < MI + NJ; ++x) load(lds + p * STAGE, x);
+      advance();
+    }
+  // Each k-block's fragments are read while the previous block's MFMAs run.
+  // Between the two blocks of k-step kt (its second fragments already in
+  // registers) a wave waits for its pieces of k-step kt + 1 (later ones stay
+  // in flight) and takes the barrier after which every wave's have landed and
+  // stage kt is free: k-step kt + NS goes there, its pieces issued between the
+  // MFMAs.  (Issued ahead of them, they and the barrier cost a lone wave of a
+  // SIMD 530 clocks per k-step, as much as the MFMAs of a 32 x 64 tile.)
+  Frags f0, f1;
+  if (nk > 0) {
+    wait_vm_groups<MI + NJ, NS - 1>(nk - 1);
+    __syncthreads();
+    read(lds, 0, f0);
+  }
+  char* st = lds;
+  for (int kt = 0; kt < nk; ++kt) {
+    read(st, 1, f1);
+    char* const next = st == lds + (NS - 1) * STAGE ? lds : st + STAGE;
+    __builtin_amdgcn_sched_barrier(0);
+    mma(f0, [](int) {});
+    WAIT_LGKMCNT(0);  // f1 (here, so that its use below waits for nothing read later)
+    if (kt + 1 < nk) {
+      wait_vm_groups<MI + NJ, NS - 2>(nk - 2 - kt);
+      __syncthreads();
+      read(next, 0, f0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    const bool refill = kt + NS < nk;
+    mma(f1, [&](int e) {
+      constexpr int PER = (MI + NJ + 3) / 4;
+      if (refill) {
+#pragma unroll
+        for (int x = 0; x < PER; ++x)
+          if (e * PER + x < MI + NJ) load(st, e * PER + x);
+      }
+    });
+    advance();
+    st = next;
   }
 
   // epilogue, straight from the accumulators
@@ -386,12 +448,16 @@ hipError_t launch(const GemmArgs* sa, int na, const GemmArgs* sb, int nb, hipStr
 
 template <int KA, int KB>
 hipError_t run_kinds(const GemmArgs* sa, int na, const GemmArgs* sb, int nb, hipStream_t s) {
-  const long cus = num_cus();
-  if (launch_tiles<KA, KB, 4, 4>(sa, na, sb, nb) >= 4 * cus)
-    return launch<KA, KB, 4, 4, 2>(sa, na, sb, nb, s);
-  if (launch_tiles<KA, KB, 2, 2>(sa, na, sb, nb) >= cus)
-    return launch<KA, KB, 2, 2, 3>(sa, na, sb, nb, s);
-  return launch<KA, KB, 1, 2, 4>(sa, na, sb, nb, s);
+  // Six tiles of 64 x 128 per CU (by the bound on the group sizes) keep every
+  // SIMD busy and halve the L2 traffic; with fewer, 32 x 64 tiles fill the CUs
+  // and pad ragged groups less.  Measured (us, 64 x 128 / 32 x 64): 4096 rows,
+  // d = 1024, H = 1408, 8 groups: GU (1584 tiles) 210 / 227, dX + dW_gu (3392)
+  // 401 / 447, down projection (576) 138 / 122; 1531 rows, d = 520, 6 groups:
+  // GU (660) 65 / 59, down projection (150) 60 / 36.  Tiles of 64 x 64 and
+  // 128 x 128 were no better than these two in any of them.
+  if (launch_tiles<KA, KB, 2, 4>(sa, na, sb, nb) >= 6L * num_cus())
+    return launch<KA, KB, 2, 4, 2>(sa, na, sb, nb, s);
+  return launch<KA, KB, 1, 2, 3>(sa, na, sb, nb, s);
 }
 
 }  // namespace

@@ -50,7 +50,7 @@ def _gemm_launch_name(ka: int, kb: int) -> str:
 _SYMBOLS = [
     (r"gemm_bf16_kernel(?:<|ILi)(\d)(?:, |ELi)(\d)", lambda m: _gemm_launch_name(int(m.group(1)), int(m.group(2)))),
     (r"gemm_bf16_kernel(?:<|ILi)(\d)", lambda m: GEMM_KINDS[int(m.group(1))]),
-    (r"gemm_f32_kernel(?:<|ILi)(\d)", lambda m: GEMM_KINDS[int(m.group(1))]),
+    (r"gemm_f32_kernel(?:<|ILi)(\d)(?:, |ELi)(\d)", lambda m: _gemm_launch_name(int(m.group(1)), int(m.group(2)))),
     (r"route_fwd_kernel", lambda m: "route_fwd"),
     (r"route_dz_kernel", lambda m: "route_dz"),
     (r"route_bwd_mfma_kernel", lambda m: "route_bwd_mfma"),

@@ -1,7 +1,7 @@
 """Grouped expert FFN of fp32 layers (forward and backward) against the oracle,
-with group sizes at the edges of the GEMM's 32-, 64- and 128-row tiles.
+with group sizes at the edges of the GEMM's 32- and 64-row tiles.
 
-The kernel takes one of three tile sizes by the number of tiles; each is
+The kernel takes one of two tile sizes by the number of tiles; each is
 reached here in every GEMM kind, with widths that leave partial column tiles,
 K extents that are no multiple of its 32-deep k-steps, empty groups, both
 expert forms, one and two sets per call, and accumulated weight gradients.
@@ -28,7 +28,7 @@ CASES = {
     "small-tiles-silu-two-sets": ([[5, 0, 40], [45]], 72, [64, 128], "silu", 1),
     "middle-tiles": ([[63, 64, 65, 0, 127, 129, 700, 1]], 520, [448], "swiglu", 1),
     "middle-tiles-silu": ([[300, 0, 511]], 264, [960], "silu", 0),
-    # enough 128 x 128 tiles in GU, dHh + dW_d / in the down projection, dX + dW_gu
+    # enough 64 x 128 tiles in GU, dHh + dW_d / in the down projection, dX + dW_gu
     "large-tiles-wide-hidden": ([[2047, 0, 129, 1601]], 72, [4096], "swiglu", 0),
     "large-tiles-wide-model": ([[1900, 127, 1801]], 4104, [64], "swiglu", 1),
 }
