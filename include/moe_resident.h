@@ -98,7 +98,8 @@ int moe_route_mask(const void* x, const void* w_router, const float* router_bias
  * moe_route_bwd_workspace_size(T, d, E) bytes; its contents on entry are
  * ignored.  In bf16 with E <= 64 and
  * d % 128 == 0 the fp32 dz enters the MFMA products as a bf16 pair hi + lo
- * (relative error <= 2^-17 per element); otherwise the sums run in fp32 FMA.
+ * (relative error <= 2^-17 per element), otherwise as three bf16 parts that
+ * hold all of it; fp32 layers multiply in fp32.
  * Every sum is taken in a fixed order, so results are run-to-run identical.
  */
 size_t moe_route_bwd_workspace_size(int T, int d, int E);

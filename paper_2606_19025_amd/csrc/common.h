@@ -85,4 +85,28 @@ DEVI bf16x8_t frag_tr(const char* base, int stride, int row0, int col0) {
   return __builtin_bit_cast(bf16x8_t, both);
 }
 
+// s_waitcnt immediate (gfx9 family): vmcnt in bits [3:0] and [15:14],
+// expcnt in [6:4], lgkmcnt in [11:8]; a field at its maximum does not wait.
+constexpr int waitcnt_imm(int vm, int lgkm) {
+  return (vm & 15) | (((vm >> 4) & 3) << 14) | (7 << 4) | ((lgkm & 15) << 8);
+}
+#define WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(waitcnt_imm((n), 15))
+#define WAIT_LGKMCNT(n) __builtin_amdgcn_s_waitcnt(waitcnt_imm(63, (n)))
+
+// Wait until at most PER * min(n, MAXN) vector memory operations are
+// outstanding; n <= 0 waits for all of them (n wave-uniform: s_waitcnt takes
+// only an immediate).
+template <int PER, int MAXN>
+DEVI void wait_vm_groups(int n) {
+  if constexpr (MAXN > 0) {
+    if (n >= MAXN) {
+      WAIT_VMCNT(PER * MAXN);
+      return;
+    }
+    wait_vm_groups<PER, MAXN - 1>(n);
+  } else {
+    WAIT_VMCNT(0);
+  }
+}
+
 __host__ __device__ inline int ceil_div(int a, int b) { return (a + b - 1) / b; }

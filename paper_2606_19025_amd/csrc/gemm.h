@@ -43,30 +43,6 @@ struct GemmArgs {
 
 DEVI int clamp_row(int v, int cap) { return v < 0 ? 0 : (v > cap ? cap : v); }
 
-// s_waitcnt immediate (gfx9 family): vmcnt in bits [3:0] and [15:14],
-// expcnt in [6:4], lgkmcnt in [11:8]; a field at its maximum does not wait.
-constexpr int waitcnt_imm(int vm, int lgkm) {
-  return (vm & 15) | (((vm >> 4) & 3) << 14) | (7 << 4) | ((lgkm & 15) << 8);
-}
-#define WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(waitcnt_imm((n), 15))
-#define WAIT_LGKMCNT(n) __builtin_amdgcn_s_waitcnt(waitcnt_imm(63, (n)))
-
-// Wait until at most PER * min(n, MAXN) vector memory operations are
-// outstanding; n <= 0 waits for all of them (n wave-uniform: s_waitcnt takes
-// only an immediate).
-template <int PER, int MAXN>
-DEVI void wait_vm_groups(int n) {
-  if constexpr (MAXN > 0) {
-    if (n >= MAXN) {
-      WAIT_VMCNT(PER * MAXN);
-      return;
-    }
-    wait_vm_groups<PER, MAXN - 1>(n);
-  } else {
-    WAIT_VMCNT(0);
-  }
-}
-
 // Group table of one set, staged in LDS once per block: the group offsets
 // clamped to [0, cap] (c), their running maximum (b: group g of an M-ragged
 // kind is rows [b[g], b[g+1])) and the number of m-tiles before group g (p).

@@ -6,7 +6,9 @@
 //   one block = 32 tokens, 8 waves.  bf16 logits use v_mfma_f32_32x32x16_bf16
 //   (tokens x experts tiles, the d reduction split over the 8 waves and summed
 //   in a fixed order through LDS; x and, for up to 64 experts, W_r rows are
-//   read whole and staged in LDS); fp32 logits use plain FMA loops.  For
+//   read whole and staged in LDS); for more experts the waves split the
+//   experts, and fp32 layers do the same on v_mfma_f32_32x32x2_f32
+//   (logits_ring).  For
 //   k <= 8 every wave then selects for 4 tokens, 16 lanes per token
 //   (select_groups, row maxima by DPP); for larger k each wave takes tokens
 //   one at a time, lane = expert, with k wave-wide (max logit, min id)
@@ -60,7 +62,29 @@ DEVI void build_local_map(const uint8_t* resident, int E, int* lmap) {
   }
 }
 
-// bf16 logits of RT_TOK tokens into zl[RT_TOK][ldz] (raw dot products).
+// z = (sum of the P partial dot products, in order, + bias) * inv_tau of the
+// block's tokens, from part [P][RT_TOK][EP], into zl[RT_TOK][ldz] and the
+// caller's logits.
+template <int EP, int P>
+DEVI void finish_logits(const RouteFwdArgs& a, int t0, const float* part, float* zl, int ldz) {
+  for (int p = threadIdx.x; p < RT_TOK * EP; p += RT_THREADS) {
+    const int i = p / EP, e = p % EP;
+    float v = part[p];
+#pragma unroll
+    for (int q = 1; q < P; ++q) v += part[q * (RT_TOK * EP) + p];
+    if (e < a.E) {
+      if (a.bias) v += a.bias[e];
+      v *= a.inv_tau;
+      zl[i * ldz + e] = v;
+      const int t = t0 + i;
+      if (a.logits && t < a.T) a.logits[(size_t)t * a.E + e] = v;
+    }
+  }
+  __syncthreads();
+}
+
+// bf16 logits of RT_TOK tokens into zl[RT_TOK][ldz], for up to 64 experts and
+// d past what logits_mfma_staged takes.
 // Wave w reduces the 64-wide slices w, w + RT_WAVES, ... of d, up to two
 // slices per round with all their loads issued before the MFMAs; the per-wave partial
 // sums are then added in wave order through LDS.
@@ -84,7 +108,8 @@ DEVI void logits_mfma(const RouteFwdArgs& a, int t0, float* zl, int ldz) {
   // chunk c of row r at chunk position c ^ ((r >> 1) & 7) so that the
   // fragment reads (16 consecutive rows, same chunk) are free of bank
   // conflicts.  The W slices stay direct fragment loads (L2-resident).
-  constexpr int UNR = NEB <= 2 ? 2 : 1;
+  static_assert(NEB <= 2, "up to 64 experts");
+  constexpr int UNR = 2;
   __shared__ __attribute__((aligned(16))) char xst[RT_WAVES][UNR][RT_TOK * 128];
   auto xswz = [](int r, int c) { return r * 128 + ((c ^ ((r >> 1) & 7)) << 4); };
   auto load_x = [&](int kb, u32x4_t* v) {
@@ -144,55 +169,20 @@ DEVI void logits_mfma(const RouteFwdArgs& a, int t0, float* zl, int ldz) {
         for (int q = 0; q < 4; ++q)
           acc[eb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[u][q], bv[u][eb][q], acc[eb], 0, 0, 0);
   }
-  // deterministic cross-wave sum (wave order).  Up to 64 experts: every wave
-  // stores its partial tile, then each thread adds its entries' RT_WAVES
-  // partials and finishes z (bias, temperature, logits store); wider expert
-  // sets add wave by wave into zl and the caller finishes z.
-  if constexpr (NEB <= 2) {
-    __shared__ float part[RT_WAVES][RT_TOK * NEB * 32];
+  // deterministic cross-wave sum (wave order): every wave stores its partial
+  // tile, then each thread adds its entries' RT_WAVES partials and finishes z
+  // (bias, temperature, logits store)
+  __shared__ float part[RT_WAVES][RT_TOK * NEB * 32];
 #pragma unroll
-    for (int eb = 0; eb < NEB; ++eb) {
+  for (int eb = 0; eb < NEB; ++eb) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int i = (r >> 2) * 8 + half * 4 + (r & 3);
-        part[wave][i * NEB * 32 + eb * 32 + row] = acc[eb][r];
-      }
-    }
-    __syncthreads();
-    for (int p = threadIdx.x; p < RT_TOK * NEB * 32; p += RT_THREADS) {
-      const int i = p / (NEB * 32), e = p % (NEB * 32);
-      float v = part[0][p];
-#pragma unroll
-      for (int wv = 1; wv < RT_WAVES; ++wv) v += part[wv][p];
-      if (e < a.E) {
-        // z = (dot + bias) * inv_tau, stored as it is summed
-        if (a.bias) v += a.bias[e];
-        v *= a.inv_tau;
-        zl[i * ldz + e] = v;
-        const int t = t0 + i;
-        if (a.logits && t < a.T) a.logits[(size_t)t * a.E + e] = v;
-      }
-    }
-    __syncthreads();
-  } else {
-    for (int wv = 0; wv < RT_WAVES; ++wv) {
-      if (wave == wv) {
-#pragma unroll
-        for (int eb = 0; eb < NEB; ++eb) {
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int i = (r >> 2) * 8 + half * 4 + (r & 3);
-            const int e = eb * 32 + row;
-            if (e < a.E) {
-              float* p = zl + i * ldz + e;
-              *p = (wv == 0) ? acc[eb][r] : *p + acc[eb][r];
-            }
-          }
-        }
-      }
-      __syncthreads();
+    for (int r = 0; r < 16; ++r) {
+      const int i = (r >> 2) * 8 + half * 4 + (r & 3);
+      part[wave][i * NEB * 32 + eb * 32 + row] = acc[eb][r];
     }
   }
+  __syncthreads();
+  finish_logits<NEB * 32, RT_WAVES>(a, t0, &part[0][0], zl, ldz);
 }
 
 // bf16 logits for up to 64 experts and d <= 64 XS RT_WAVES.  Wave w reduces
@@ -285,38 +275,124 @@ DEVI void logits_mfma_staged(const RouteFwdArgs& a, int t0, float* zl, int ldz) 
     }
   }
   __syncthreads();
-  for (int p = threadIdx.x; p < RT_TOK * NEB * 32; p += RT_THREADS) {
-    const int i = p / (NEB * 32), e = p % (NEB * 32);
-    float v = part[p];
-#pragma unroll
-    for (int wv = 1; wv < RT_WAVES; ++wv) v += part[wv * (RT_TOK * NEB * 32) + p];
-    if (e < a.E) {
-      // z = (dot + bias) * inv_tau, stored as it is summed
-      if (a.bias) v += a.bias[e];
-      v *= a.inv_tau;
-      zl[i * ldz + e] = v;
-      const int t = t0 + i;
-      if (a.logits && t < a.T) a.logits[(size_t)t * a.E + e] = v;
-    }
-  }
-  __syncthreads();
+  finish_logits<NEB * 32, RT_WAVES>(a, t0, part, zl, ldz);
 }
 
-DEVI void logits_f32(const RouteFwdArgs& a, int t0, float* zl, int ldz) {
-  const float* x = static_cast<const float*>(a.x);
-  const float* w = static_cast<const float*>(a.w);
-  for (int p = threadIdx.x; p < RT_TOK * a.E; p += RT_THREADS) {
-    const int i = p / a.E, e = p % a.E;
-    const int t = t0 + i;
-    float s = 0.f;
-    if (t < a.T) {
-      const float* xr = x + (size_t)t * a.d;
-      const float* wr = w + (size_t)e * a.d;
-      for (int c = 0; c < a.d; ++c) s = fmaf(xr[c], wr[c], s);
+// Address of zeros for k past the last (16 bytes).
+__device__ __attribute__((aligned(16))) const uint32_t kRouteZeros[4] = {0u, 0u, 0u, 0u};
+
+// 16 (or 4) bytes per lane at p -> LDS at base + 16 (4) lane, base wave-uniform.
+// The asm sets m0 and leaves the one wait state an LDS DMA needs after it.
+template <bool VEC>
+DEVI void route_dma(const void* p, char* base) {
+  const unsigned m0 = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(lds_void_t*)base);
+  if constexpr (VEC)
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(p), "s"(m0)
+                 : "m0", "memory");
+  else
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" ::"v"(p), "s"(m0)
+                 : "m0", "memory");
+}
+
+// Logits of fp32 layers, and of bf16 ones with more than 64 experts.  The waves
+// form EG expert groups (32 experts each) x KG = 8 / EG groups of d slices: a
+// wave's 32 x 32 tile of (token, expert) runs over the slices kg, kg + KG, ...
+// of 128 bytes, so W_r is read once per block, each row by one wave, and only
+// KG partial sums are left to add.  (One wave for all experts of a d slice held
+// 128 accumulators at 256 experts and added them to LDS wave after wave:
+// 5003 tokens, d = 1536, 256 experts took 82 us.  fp32 dot products by one
+// thread each read every operand element with a load of its own.)
+// x and W_r rows go to LDS by DMA as whole 128-byte pieces through a ring of NS
+// stages.  Chunk c (16 bytes) of row r sits at chunk c ^ ((r >> 1) & 7).
+// bf16: v_mfma_f32_32x32x16_bf16; fp32: v_mfma_f32_32x32x2_f32.  Four
+// accumulators in turn keep the chains of additions short.  VEC: rows are
+// 16-byte aligned; otherwise the DMA moves 4 bytes per lane.  The 256-expert
+// case above now takes 31 us, bound by each CU's read of W_r (786 KB) from L2.
+template <class T, int EG, bool VEC>
+DEVI void logits_ring(const RouteFwdArgs& a, int t0, float* zl, int ldz) {
+  constexpr int KG = RT_WAVES / EG;
+  constexpr int EP = EG * 32;
+  constexpr int KW = 128 / sizeof(T);             // elements of a slice
+  constexpr int W_BYTES = RT_WAVES * 4096;        // each wave's 32 W_r rows
+  constexpr int STAGE = W_BYTES + KG * 4096;      // and the KG slices' 32 x rows
+  constexpr int NS = EG == 1 ? 2 : 3;
+  constexpr int XP = KG >= 2 ? KG / 2 : 1;        // KiB of x per wave and stage
+  constexpr int PER = (4 + XP) * (VEC ? 1 : 4);   // DMA loads per wave and stage
+  static_assert(NS * STAGE >= KG * RT_TOK * EP * 4, "the partial sums reuse the ring");
+  __shared__ __attribute__((aligned(1024))) char ring[NS * STAGE];
+  const T* x = static_cast<const T*>(a.x);
+  const T* w = static_cast<const T*>(a.w);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int eg = wave % EG, kg = wave / EG;
+  const int n_slices = (a.d + KW - 1) / KW;
+  const int n_stages = (n_slices + KG - 1) / KG;
+  // one KiB (8 rows of 128 bytes, from row r0) of slice sl of p into dst; row
+  // index clamped to the last (the results of the rows past it are not used)
+  auto kib = [&](const T* p, int r0, int last, int sl, char* dst) {
+    if constexpr (VEC) {
+      const int r = r0 + (lane >> 3);
+      const int c = ((lane & 7) ^ ((r >> 1) & 7)) * (16 / (int)sizeof(T)) + sl * KW;
+      route_dma<true>(c < a.d ? (const void*)(p + (size_t)min(r, last) * a.d + c) : kRouteZeros, dst);
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int r = r0 + 2 * q + (lane >> 5);
+        const int ch = ((lane >> 2) & 7) ^ ((r >> 1) & 7);
+        const int c = ch * 4 + (lane & 3) + sl * KW;
+        route_dma<false>(c < a.d ? (const void*)(p + (size_t)min(r, last) * a.d + c) : kRouteZeros,
+                         dst + q * 256);
+      }
     }
-    zl[i * ldz + e] = s;
+  };
+  auto load = [&](int stage) {
+    char* st = ring + stage % NS * STAGE;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      kib(w, eg * 32 + 8 * i, a.E - 1, stage * KG + kg, st + wave * 4096 + i * 1024);
+#pragma unroll
+    for (int i = 0; i < XP; ++i) {
+      // the block's 4 KG KiB of x (EG = 8: waves w and w + 4 bring the same one)
+      const int q = (wave * XP + i) % (4 * KG);
+      kib(x, t0 + 8 * (q & 3), a.T - 1, stage * KG + (q >> 2), st + W_BYTES + q * 1024);
+    }
+  };
+  f32x16_t acc[4] = {f32x16_t{}, f32x16_t{}, f32x16_t{}, f32x16_t{}};
+  const int row = lane & 31, half = lane >> 5;
+#pragma unroll
+  for (int p = 0; p < NS - 1; ++p)
+    if (p < n_stages) load(p);
+  for (int s = 0; s < n_stages; ++s) {
+    wait_vm_groups<PER, NS - 2>(n_stages - 1 - s);
+    __syncthreads();  // stage s is whole; everyone is done with stage s - 1
+    if (s + NS - 1 < n_stages) load(s + NS - 1);
+    const char* wl = ring + s % NS * STAGE + wave * 4096;
+    const char* xl = ring + s % NS * STAGE + W_BYTES + kg * 4096;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int o = row * 128 + (((2 * q + half) ^ ((row >> 1) & 7)) << 4);
+      if constexpr (sizeof(T) == 2) {
+        acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8_t*>(xl + o),
+                                                         *reinterpret_cast<const bf16x8_t*>(wl + o),
+                                                         acc[q], 0, 0, 0);
+      } else {
+        const f32x4_t xv = *reinterpret_cast<const f32x4_t*>(xl + o);
+        const f32x4_t wv = *reinterpret_cast<const f32x4_t*>(wl + o);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          acc[e] = __builtin_amdgcn_mfma_f32_32x32x2f32(xv[e], wv[e], acc[e], 0, 0, 0);
+      }
+    }
+  }
+  __syncthreads();  // the partial sums take the ring's place
+  float* part = reinterpret_cast<float*>(ring);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int i = (r >> 2) * 8 + half * 4 + (r & 3);
+    part[(kg * RT_TOK + i) * EP + eg * 32 + row] = (acc[0][r] + acc[1][r]) + (acc[2][r] + acc[3][r]);
   }
   __syncthreads();
+  finish_logits<EP, KG>(a, t0, part, zl, ldz);
 }
 
 // Logit as read for selection: NaN ranks as -inf (some expert is always
@@ -411,8 +487,13 @@ DEVI void select_groups(const RouteFwdArgs& a, const float* zl, int t0, const in
   }
 }
 
-// XS > 0: bf16 with up to 64 experts and d <= 64 XS RT_WAVES (logits_mfma_staged)
-template <int NEB, bool BF16, int XS>
+// Which logits path a block takes: STAGED4 / STAGED8 bf16, up to 64 experts
+// and d <= 64 * 4 / 64 * 8 * RT_WAVES; DIRECT bf16, up to 64 experts, longer d;
+// RING bf16 beyond 64 experts; RING_F32 fp32 with 16-byte aligned rows,
+// RING_F32_DWORD fp32 otherwise.
+enum RoutePath { STAGED4, STAGED8, DIRECT, RING, RING_F32, RING_F32_DWORD };
+
+template <int NEB, int PATH>
 __global__ __launch_bounds__(RT_THREADS) void route_fwd_kernel(RouteFwdArgs a) {
   constexpr int LDZ = NEB * 32 + 1;
   constexpr int NQ = (NEB * 32 + 63) / 64;  // logits (and selections) per lane
@@ -422,21 +503,12 @@ __global__ __launch_bounds__(RT_THREADS) void route_fwd_kernel(RouteFwdArgs a) {
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   if (wave == 0) build_local_map(a.resident, a.E, lmap);
-  if constexpr (XS > 0) logits_mfma_staged<NEB, XS>(a, t0, zl, LDZ);
-  else if constexpr (BF16) logits_mfma<NEB>(a, t0, zl, LDZ);
-  else logits_f32(a, t0, zl, LDZ);
-  // z = (dot + bias) * inv_tau (the bf16 logits paths finish it for up to 64 experts)
-  constexpr bool z_done = BF16 && NEB <= 2;
-  for (int p = threadIdx.x; !z_done && p < RT_TOK * a.E; p += RT_THREADS) {
-    const int i = p / a.E, e = p % a.E;
-    float v = zl[i * LDZ + e];
-    if (a.bias) v += a.bias[e];
-    v *= a.inv_tau;
-    zl[i * LDZ + e] = v;
-    const int t = t0 + i;
-    if (a.logits && t < a.T) a.logits[(size_t)t * a.E + e] = v;
-  }
-  if constexpr (!z_done) __syncthreads();  // (those paths end with one)
+  // every path ends with a barrier
+  if constexpr (PATH == STAGED4) logits_mfma_staged<NEB, 4>(a, t0, zl, LDZ);
+  else if constexpr (PATH == STAGED8) logits_mfma_staged<NEB, 8>(a, t0, zl, LDZ);
+  else if constexpr (PATH == DIRECT) logits_mfma<NEB>(a, t0, zl, LDZ);
+  else if constexpr (PATH == RING) logits_ring<bf16_t, NEB, true>(a, t0, zl, LDZ);
+  else logits_ring<float, NEB, PATH == RING_F32>(a, t0, zl, LDZ);
 
   if (a.k <= RT_KSEL) {
     static_assert(RT_TOK == 4 * RT_WAVES, "16 lanes per token in every wave");
@@ -524,10 +596,12 @@ struct RouteBwdArgs {
   float* db;
   void* dx;
   float* part_w;  // [n_chunks][E][d]
-  float* part_b;  // [n_chunks][n_bparts][E]
+  float* part_b;  // [n_chunks][n_bparts][E], or NULL (no d_bias wanted)
   int T, d, E, k, gate, accumulate_dx, n_chunks;
   int n_bparts;   // d_bias partial sums per chunk
   float inv_tau;
+  float part_scale;  // factor of the partial sums: 1, or inv_tau when the only
+                     // chunk's are the results (part_w = dw, part_b = db)
 };
 
 constexpr int RB_CHUNK = 256;  // tokens per partial sum of dW_r
@@ -550,89 +624,54 @@ __global__ __launch_bounds__(256) void route_dz_kernel(RouteBwdArgs a) {
     for (int e = lane; e < a.E; e += 64) acc += expf(a.logits[(size_t)t * a.E + e] - zmax);
     denom = wave_sum(acc);
   }
-  for (int e = lane; e < a.E; e += 64) {
-    int jj = -1;
-    for (int j = 0; j < a.k; ++j)
-      if (a.idx[o + j] == e) { jj = j; break; }
+  // lane j holds route j's expert and the route's own share of the gradient
+  // (k <= 64; with more, the lane of the expert looks its route up)
+  const bool held = a.k <= 64;
+  auto share = [&](int j) {
+    const float wv = a.tw[o + j], dv = a.dtw[o + j];
+    return a.gate == 0 ? wv * (dv - s) : a.gate == 2 ? dv * wv * (1.f - wv) : dv;
+  };
+  const int my_e = held && lane < a.k ? a.idx[o + lane] : -1;
+  const float my_g = held && lane < a.k ? share(lane) : 0.f;
+  for (int e = lane; e - lane < a.E; e += 64) {
     float g = 0.f;
-    if (a.gate == 0) {
-      if (jj >= 0) g = a.tw[o + jj] * (a.dtw[o + jj] - s);
-    } else if (a.gate == 2) {
-      if (jj >= 0) { const float wv = a.tw[o + jj]; g = a.dtw[o + jj] * wv * (1.f - wv); }
+    if (held) {
+      for (int j = a.k - 1; j >= 0; --j) {
+        const int ej = __builtin_amdgcn_readlane(my_e, j);
+        const float gj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_g), j));
+        if (ej == e) g = gj;
+      }
     } else {
-      const float p = expf(a.logits[(size_t)t * a.E + e] - zmax) / denom;
-      g = p * ((jj >= 0 ? a.dtw[o + jj] : 0.f) - s);
+      for (int j = a.k - 1; j >= 0; --j)
+        if (a.idx[o + j] == e) g = share(j);
     }
-    a.dz[(size_t)t * a.E + e] = g;
+    if (e < a.E) {
+      if (a.gate == 1) g = expf(a.logits[(size_t)t * a.E + e] - zmax) / denom * (g - s);
+      a.dz[(size_t)t * a.E + e] = g;
+    }
   }
 }
 
-// partial[c][e][col] = sum_{t in chunk c} dz[t,e] x[t,col]; block = 64 cols x
-// 64 experts of one chunk, thread = 4 experts x 4 cols.
-template <class T>
-__global__ __launch_bounds__(256) void route_dw_partial_kernel(RouteBwdArgs a) {
-  __shared__ float sdz[32][65];
-  __shared__ float sx[32][65];
-  const T* x = static_cast<const T*>(a.x);
-  const int c0 = blockIdx.x * 64;
-  const int e0 = blockIdx.y * 64;
-  const int chunk = blockIdx.z;
-  const int tb = chunk * RB_CHUNK;
-  const int te = min(a.T, tb + RB_CHUNK);
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  float acc[4][4] = {};
-  float bacc = 0.f;
-  for (int t1 = tb; t1 < te; t1 += 32) {
-    for (int p = threadIdx.x; p < 32 * 64; p += 256) {
-      const int i = p >> 6, c = p & 63;
-      const int t = t1 + i;
-      sdz[i][c] = (t < te && e0 + c < a.E) ? a.dz[(size_t)t * a.E + e0 + c] : 0.f;
-      sx[i][c] = (t < te && c0 + c < a.d) ? to_f32(x[(size_t)t * a.d + c0 + c]) : 0.f;
-    }
-    __syncthreads();
-    for (int i = 0; i < 32; ++i) {
-      float zv[4], xv[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) { zv[u] = sdz[i][ty * 4 + u]; xv[u] = sx[i][tx * 4 + u]; }
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) acc[u][v] = fmaf(zv[u], xv[v], acc[u][v]);
-    }
-    if (blockIdx.x == 0 && threadIdx.x < 64)
-      for (int i = 0; i < 32; ++i) bacc += sdz[i][threadIdx.x];
-    __syncthreads();
-  }
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int e = e0 + ty * 4 + u;
-    if (e >= a.E) continue;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int c = c0 + tx * 4 + v;
-      if (c < a.d) a.part_w[((size_t)chunk * a.E + e) * a.d + c] = acc[u][v];
-    }
-  }
-  if (blockIdx.x == 0 && threadIdx.x < 64 && e0 + (int)threadIdx.x < a.E)
-    a.part_b[(size_t)chunk * a.n_bparts * a.E + e0 + threadIdx.x] = bacc;
-}
-
+// V = 4: 16 bytes per load and store (E d % 4 == 0, 16-byte aligned dw).
+template <int V>
 __global__ __launch_bounds__(256) void route_dw_reduce_kernel(RouteBwdArgs a) {
   // dW_r[i] = inv_tau * (((p_0[i] + p_1[i]) + p_2[i]) + ...); the chunk
   // loads of a thread are issued 8 at a time
-  const size_t n = (size_t)a.E * a.d;
+  typedef __attribute__((__vector_size__(V * 4))) float vec;
+  const size_t n = (size_t)a.E * a.d / V;
+  const vec* part = reinterpret_cast<const vec*>(a.part_w);
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) {
-    float s = 0.f;
+    vec s = {};
     int c = 0;
     for (; c + 8 <= a.n_chunks; c += 8) {
-      float v[8];
+      vec v[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = a.part_w[(size_t)(c + u) * n + i];
+      for (int u = 0; u < 8; ++u) v[u] = part[(size_t)(c + u) * n + i];
 #pragma unroll
       for (int u = 0; u < 8; ++u) s += v[u];
     }
-    for (; c < a.n_chunks; ++c) s += a.part_w[(size_t)c * n + i];
-    a.dw[i] = s * a.inv_tau;
+    for (; c < a.n_chunks; ++c) s += part[(size_t)c * n + i];
+    reinterpret_cast<vec*>(a.dw)[i] = s * a.inv_tau;
   }
   if (a.db && blockIdx.x == 0) {
     // d_bias[e] = inv_tau * sum of the (chunk, part) partials: four
@@ -664,57 +703,12 @@ __global__ __launch_bounds__(256) void route_dw_reduce_kernel(RouteBwdArgs a) {
   }
 }
 
-// dx[t, c..c+V) (+)= inv_tau * sum_e dz[t,e] W_r[e, c..c+V); block = 8 tokens,
-// thread = 8 tokens x one 16-byte column vector.
-template <class T>
-__global__ __launch_bounds__(256) void route_dx_kernel(RouteBwdArgs a) {
-  constexpr int V = Vec16<T>::N;
-  constexpr int TT = 8;
-  __shared__ float sdz[TT][257];
-  const T* w = static_cast<const T*>(a.w);
-  T* dx = static_cast<T*>(a.dx);
-  const int t0 = blockIdx.x * TT;
-  for (int p = threadIdx.x; p < TT * a.E; p += 256) {
-    const int i = p / a.E, e = p % a.E;
-    sdz[i][e] = (t0 + i < a.T) ? a.dz[(size_t)(t0 + i) * a.E + e] : 0.f;
-  }
-  __syncthreads();
-  for (int c = threadIdx.x * V; c < a.d; c += 256 * V) {
-    float acc[TT][V];
-#pragma unroll
-    for (int i = 0; i < TT; ++i)
-#pragma unroll
-      for (int u = 0; u < V; ++u) acc[i][u] = 0.f;
-    for (int e = 0; e < a.E; ++e) {
-      float wv[V];
-      load16_f32(w + (size_t)e * a.d + c, wv);
-#pragma unroll
-      for (int i = 0; i < TT; ++i) {
-        const float z = sdz[i][e];
-#pragma unroll
-        for (int u = 0; u < V; ++u) acc[i][u] = fmaf(z, wv[u], acc[i][u]);
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < TT; ++i) {
-      const int t = t0 + i;
-      if (t >= a.T) break;
-      T* p = dx + (size_t)t * a.d + c;
-      float o[V];
-      if (a.accumulate_dx) load16_f32(p, o);
-#pragma unroll
-      for (int u = 0; u < V; ++u) o[u] = (a.accumulate_dx ? o[u] : 0.f) + a.inv_tau * acc[i][u];
-      store16_f32(p, o);
-    }
-  }
-}
-
-// bf16 router backward on MFMA (E <= 64, d % 128 == 0): one block = 128
-// columns x RB_CHUNK tokens, in sub-chunks of 64 tokens.  Per sub-chunk the
+// bf16 router backward on MFMA (E <= 64): one block = 128 columns (the last
+// ones may lie past d) x RB_CHUNK tokens, in sub-chunks of 64 tokens.  Per sub-chunk the
 // block stages x[tokens, cols] and dz[tokens, 0..63] in LDS, the fp32 dz split
-// into a bf16 pair hi + lo (|dz - hi - lo| <= 2^-17 |dz|), and computes
-//   dW partial[e, c] += sum_t (hi + lo)[t, e] x[t, c]            (k = tokens)
-//   dx[t, c] (+)= inv_tau * sum_e (hi + lo)[t, e] W_r[e, c]       (k = experts)
+// into NP bf16 parts, and computes
+//   dW partial[e, c] += sum_t (parts)[t, e] x[t, c]            (k = tokens)
+//   dx[t, c] (+)= inv_tau * sum_e (parts)[t, e] W_r[e, c]       (k = experts)
 // with v_mfma_f32_32x32x16_bf16; wave w owns columns 32w..32w+31 of both.
 // The next sub-chunk's x and dz are loaded into registers while the current
 // one is computed; the dx result is staged through LDS so that the update of
@@ -730,7 +724,6 @@ constexpr int RBM_XS = RBM_COLS * 2 + 64;     // x row stride (bytes): the 4 row
 constexpr int RBM_ZS = 64 * 2 + 16;           // dz row stride: 16 rows of a 16-byte
                                               // read on distinct banks
 constexpr int RBM_WS = RBM_COLS * 2 + 64;     // W_r row stride
-constexpr int RBM_LDS = RBM_SUB * RBM_XS + 2 * RBM_SUB * RBM_ZS + 64 * RBM_WS;
 constexpr int RBM_STG = RBM_COLS + 4;  // fp32 row stride of the staged dx update
 static_assert(RBM_SUB * RBM_STG * 4 <= RBM_SUB * RBM_XS + 2 * RBM_SUB * RBM_ZS,
               "the staged dx update must fit over the x and dz tiles");
@@ -739,12 +732,39 @@ constexpr int RBM_ZV = RBM_SUB * 64 / 8 / 256;        // 8-expert dz groups per 
 static_assert(RBM_XV * 256 * 8 == RBM_SUB * RBM_COLS && RBM_ZV * 256 * 8 == RBM_SUB * 64,
               "staging split");
 
+// v as a sum of NP bf16 values: |v - sum| <= 2^-17 |v| for 2, nothing left for 3.
+template <int NP>
+DEVI void split_bf16(float v, bf16_t* out) {
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    out[p] = (bf16_t)v;
+    v -= (float)out[p];
+  }
+}
+
+// The same over 8 values, to LDS: part p at dst + p stride.
+template <int NP>
+DEVI void store_split8(const float* v, char* dst, int stride) {
+  bf16x8_t o[NP];
+#pragma unroll
+  for (int u = 0; u < 8; ++u) {
+    bf16_t q[NP];
+    split_bf16<NP>(v[u], q);
+#pragma unroll
+    for (int p = 0; p < NP; ++p) o[p][u] = q[p];
+  }
+#pragma unroll
+  for (int p = 0; p < NP; ++p) *reinterpret_cast<bf16x8_t*>(dst + p * stride) = o[p];
+}
+
+// NP = 2 where d % 128 == 0; ragged d takes 3 parts (nothing of dz is lost).
+template <int NP>
 __global__ __launch_bounds__(256, 2) void route_bwd_mfma_kernel(RouteBwdArgs a) {
-  __shared__ __attribute__((aligned(16))) char lds[RBM_LDS];
+  constexpr int ZB = RBM_SUB * RBM_ZS;  // bytes of one part of dz
+  __shared__ __attribute__((aligned(16))) char lds[RBM_SUB * RBM_XS + NP * ZB + 64 * RBM_WS];
   char* xs = lds;
-  char* zh = xs + RBM_SUB * RBM_XS;
-  char* zl = zh + RBM_SUB * RBM_ZS;
-  char* wl = zl + RBM_SUB * RBM_ZS;
+  char* zs = xs + RBM_SUB * RBM_XS;
+  char* wl = zs + NP * ZB;
   const bf16_t* x = static_cast<const bf16_t*>(a.x);
   const bf16_t* w = static_cast<const bf16_t*>(a.w);
   bf16_t* dx = static_cast<bf16_t*>(a.dx);
@@ -761,7 +781,7 @@ __global__ __launch_bounds__(256, 2) void route_bwd_mfma_kernel(RouteBwdArgs a) 
   for (int p = tid; p < 64 * (RBM_COLS / 8); p += 256) {
     const int e = p / (RBM_COLS / 8), c = (p % (RBM_COLS / 8)) * 8;
     *reinterpret_cast<u32x4_t*>(wl + e * RBM_WS + c * 2) =
-        e < a.E ? *reinterpret_cast<const u32x4_t*>(w + (size_t)e * a.d + c0 + c) : zero4;
+        e < a.E && c0 + c < a.d ? *reinterpret_cast<const u32x4_t*>(w + (size_t)e * a.d + c0 + c) : zero4;
   }
 
   // register staging of one sub-chunk: thread owns x vectors p = tid + 256 v
@@ -769,12 +789,13 @@ __global__ __launch_bounds__(256, 2) void route_bwd_mfma_kernel(RouteBwdArgs a) 
   // experts 8 (p % 8)..)
   u32x4_t xr[RBM_XV];
   float zr[RBM_ZV][8];
+  const bool col_ok = c0 + (tid & 15) * 8 < a.d;  // this thread's 8 columns
   auto load_sub = [&](int t0) {
 #pragma unroll
     for (int v = 0; v < RBM_XV; ++v) {
       const int p = tid + 256 * v;
       const int t = t0 + (p >> 4);
-      xr[v] = t < a.T ? *reinterpret_cast<const u32x4_t*>(x + (size_t)t * a.d + c0 + (p & 15) * 8)
+      xr[v] = t < a.T && col_ok ? *reinterpret_cast<const u32x4_t*>(x + (size_t)t * a.d + c0 + (p & 15) * 8)
                       : zero4;
     }
 #pragma unroll
@@ -802,15 +823,7 @@ __global__ __launch_bounds__(256, 2) void route_bwd_mfma_kernel(RouteBwdArgs a) 
 #pragma unroll
     for (int v = 0; v < RBM_ZV; ++v) {
       const int p = tid + 256 * v;
-      bf16x8_t hi, lo;
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const bf16_t h = (bf16_t)zr[v][u];
-        hi[u] = h;
-        lo[u] = (bf16_t)(zr[v][u] - (float)h);
-      }
-      *reinterpret_cast<bf16x8_t*>(zh + (p >> 3) * RBM_ZS + (p & 7) * 16) = hi;
-      *reinterpret_cast<bf16x8_t*>(zl + (p >> 3) * RBM_ZS + (p & 7) * 16) = lo;
+      store_split8<NP>(zr[v], zs + (p >> 3) * RBM_ZS + (p & 7) * 16, ZB);
     }
   };
 
@@ -820,7 +833,7 @@ __global__ __launch_bounds__(256, 2) void route_bwd_mfma_kernel(RouteBwdArgs a) 
   // sub-chunks s with s % n_bparts == b, from the registers that stage them:
   // per thread its two rows, then across the 8 lanes of an expert group
   // (xor shuffles), then (at the end) across the 4 waves in wave order
-  const bool do_bias = (int)blockIdx.x < a.n_bparts;
+  const bool do_bias = a.part_b && (int)blockIdx.x < a.n_bparts;
   float bacc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   for (int sc = 0; sc < n_sub; ++sc) {
     const int t0 = chunk * RB_CHUNK + sc * RBM_SUB;
@@ -843,7 +856,7 @@ __global__ __launch_bounds__(256, 2) void route_bwd_mfma_kernel(RouteBwdArgs a) 
     // old dx of this thread's 16-byte chunks of the sub-chunk (requested
     // before the MFMAs; used by the coalesced update below)
     u32x4_t old[RBM_XV];
-    if (a.accumulate_dx) {
+    if (a.accumulate_dx && col_ok) {
 #pragma unroll
       for (int v = 0; v < RBM_XV; ++v) {
         const int p = tid + 256 * v;
@@ -858,10 +871,10 @@ __global__ __launch_bounds__(256, 2) void route_bwd_mfma_kernel(RouteBwdArgs a) 
       const bf16x8_t bx = frag_tr(xs, RBM_XS, ks * 16, wave * 32);
 #pragma unroll
       for (int eb = 0; eb < 2; ++eb) {
-        const bf16x8_t ah = frag_tr(zh, RBM_ZS, ks * 16, eb * 32);
-        const bf16x8_t al = frag_tr(zl, RBM_ZS, ks * 16, eb * 32);
-        accw[eb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bx, ah, accw[eb], 0, 0, 0);
-        accw[eb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bx, al, accw[eb], 0, 0, 0);
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+          accw[eb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+              bx, frag_tr(zs + p * ZB, RBM_ZS, ks * 16, eb * 32), accw[eb], 0, 0, 0);
       }
     }
 
@@ -874,10 +887,10 @@ __global__ __launch_bounds__(256, 2) void route_bwd_mfma_kernel(RouteBwdArgs a) 
       for (int tb = 0; tb < 2; ++tb) {
         const int r = tb * 32 + (lane & 31);
         const int e = ks * 16 + 8 * (lane >> 5);
-        const bf16x8_t ah = *reinterpret_cast<const bf16x8_t*>(zh + r * RBM_ZS + e * 2);
-        const bf16x8_t al = *reinterpret_cast<const bf16x8_t*>(zl + r * RBM_ZS + e * 2);
-        accx[tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bw, ah, accx[tb], 0, 0, 0);
-        accx[tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bw, al, accx[tb], 0, 0, 0);
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+          accx[tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+              bw, *reinterpret_cast<const bf16x8_t*>(zs + p * ZB + r * RBM_ZS + e * 2), accx[tb], 0, 0, 0);
       }
     }
     // lane holds dx[t0 + 32 tb + lane%32][c0 + 32 wave + 8q + 4(lane/32) + 0..3];
@@ -900,7 +913,7 @@ __global__ __launch_bounds__(256, 2) void route_bwd_mfma_kernel(RouteBwdArgs a) 
       const int p = tid + 256 * v;
       const int r = p >> 4, c = (p & 15) * 8;
       const int t = t0 + r;
-      if (t >= a.T) continue;
+      if (t >= a.T || !col_ok) continue;
       const f32x4_t lo = *reinterpret_cast<const f32x4_t*>(stg + r * RBM_STG + c);
       const f32x4_t hi = *reinterpret_cast<const f32x4_t*>(stg + r * RBM_STG + c + 4);
       const bf16x8_t ob = __builtin_bit_cast(bf16x8_t, old[v]);
@@ -921,11 +934,12 @@ __global__ __launch_bounds__(256, 2) void route_bwd_mfma_kernel(RouteBwdArgs a) 
     if (e >= a.E) continue;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
+      if (c0 + wave * 32 + 8 * q + 4 * (lane >> 5) >= a.d) continue;
       float* p = a.part_w + ((size_t)chunk * a.E + e) * a.d + c0 + wave * 32 + 8 * q +
                  4 * (lane >> 5);
       const f32x4_t o = {accw[eb][4 * q], accw[eb][4 * q + 1], accw[eb][4 * q + 2],
                          accw[eb][4 * q + 3]};
-      *reinterpret_cast<f32x4_t*>(p) = o;
+      *reinterpret_cast<f32x4_t*>(p) = o * a.part_scale;
     }
   }
   if (do_bias) {
@@ -937,7 +951,314 @@ __global__ __launch_bounds__(256, 2) void route_bwd_mfma_kernel(RouteBwdArgs a) 
     __syncthreads();
     if (tid < a.E)
       a.part_b[((size_t)chunk * a.n_bparts + blockIdx.x) * a.E + tid] =
-          ((bpart[0][tid] + bpart[1][tid]) + bpart[2][tid]) + bpart[3][tid];
+          (((bpart[0][tid] + bpart[1][tid]) + bpart[2][tid]) + bpart[3][tid]) * a.part_scale;
+  }
+}
+
+// d_bias partial of this block: rows[r][e], r < R (EP experts each, in LDS), are
+// its threads' shares; added in row order.
+template <int EP, int R>
+DEVI void store_bias(const RouteBwdArgs& a, int chunk, const float* rows) {
+  if ((int)threadIdx.x >= a.E) return;
+  float s = 0.f;
+#pragma unroll 8
+  for (int r = 0; r < R; ++r) s += rows[r * EP + threadIdx.x];
+  a.part_b[((size_t)chunk * a.n_bparts + blockIdx.x) * a.E + threadIdx.x] = s * a.part_scale;
+}
+
+// 8 (or 4) experts e0.. of dz row t into v; zeros past E and T.
+template <int N>
+DEVI void load_dz(const RouteBwdArgs& a, int t, int e0, bool vec, float* v) {
+  const float* src = a.dz + (size_t)t * a.E + e0;
+  if (t < a.T && vec && e0 + N <= a.E) {
+#pragma unroll
+    for (int q = 0; q < N / 4; ++q) {
+      const f32x4_t u = *reinterpret_cast<const f32x4_t*>(src + 4 * q);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[4 * q + e] = u[e];
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < N; ++e) v[e] = t < a.T && e0 + e < a.E ? src[e] : 0.f;
+  }
+}
+
+// v_mfma_f32_16x16x32 operand fragment (lane l: index i0 + l % 16, k = k0 +
+// 8 (l / 16) + 0..7) of an LDS array whose rows are k (see frag_tr).
+DEVI bf16x8_t frag_tr16(const char* base, int stride, int k0, int i0) {
+  const int lane = threadIdx.x & 63;
+  const int g = lane >> 4, i = lane & 15;
+  s16x4_t v[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+    v[h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(
+        base + (size_t)(k0 + 8 * g + 4 * h + (i >> 2)) * stride + (i0 + 4 * (i & 3)) * 2));
+  const s16x8_t both = __builtin_shufflevector(v[0], v[1], 0, 1, 2, 3, 4, 5, 6, 7);
+  return __builtin_bit_cast(bf16x8_t, both);
+}
+
+constexpr int RBW_COLS = 64;  // columns per block of the two kernels below
+
+// The same for 65 to 256 experts (EP = 128 or 256): 8 waves, 64 columns x
+// RB_CHUNK tokens, all EP experts of W_r's columns and of 64 tokens' dz in LDS.
+// Wave (quarter, half) computes dW of a quarter of the experts and dx of a
+// quarter of the tokens, for half of the columns, on 16 x 16 x 32 MFMAs with dz
+// in 3 bf16 parts (its whole fp32 value).  5003 tokens, d = 1536, 256 experts:
+// 49 us; the VALU kernels this replaces took 364 (dW partials) + 108 us (dx),
+// bound by their LDS and L2 operand reads.
+template <int EP>
+__global__ __launch_bounds__(512) void route_bwd_wide_kernel(RouteBwdArgs a) {
+  constexpr int SUB = RBM_SUB, XS = RBW_COLS * 2 + 32, ZS = EP * 2 + 16;
+  constexpr int G = EP / 8, ZR = 512 / G, ZV = SUB / ZR;  // dz: 8-expert groups, rows per pass, passes
+  constexpr int EQ = EP / 4, ET = EQ / 16;
+  constexpr int NP = 3, ZB = SUB * ZS;  // parts of dz, bytes of one
+  __shared__ __attribute__((aligned(16))) char lds[SUB * XS + NP * ZB + EP * XS];
+  char* xs = lds;
+  char* zs = xs + SUB * XS;
+  char* wl = zs + NP * ZB;
+  static_assert(ZR * EP * 4 <= NP * ZB, "the bias shares fit over dz");
+  const bf16_t* x = static_cast<const bf16_t*>(a.x);
+  const bf16_t* w = static_cast<const bf16_t*>(a.w);
+  bf16_t* dx = static_cast<bf16_t*>(a.dx);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l16 = lane & 15, g4 = lane >> 4;
+  const int quarter = wave >> 1, col0 = (wave & 1) * 32;
+  const int c0 = blockIdx.x * RBW_COLS, chunk = blockIdx.y;
+  const int n_sub = (min(RB_CHUNK, a.T - chunk * RB_CHUNK) + SUB - 1) / SUB;
+  const bool vec_dz = (a.E & 3) == 0 && ((uintptr_t)a.dz & 15) == 0;
+  const u32x4_t zero4 = {0u, 0u, 0u, 0u};
+  for (int p = tid; p < EP * 8; p += 512) {
+    const int e = p >> 3, c = (p & 7) * 8;
+    *reinterpret_cast<u32x4_t*>(wl + e * XS + c * 2) =
+        e < a.E && c0 + c < a.d ? *reinterpret_cast<const u32x4_t*>(w + (size_t)e * a.d + c0 + c) : zero4;
+  }
+  u32x4_t xr;
+  float zr[ZV][8];
+  auto load_sub = [&](int t0) {
+    const int t = t0 + (tid >> 3), c = c0 + (tid & 7) * 8;
+    xr = t < a.T && c < a.d ? *reinterpret_cast<const u32x4_t*>(x + (size_t)t * a.d + c) : zero4;
+#pragma unroll
+    for (int v = 0; v < ZV; ++v) load_dz<8>(a, t0 + tid / G + v * ZR, tid % G * 8, vec_dz, zr[v]);
+  };
+  auto store_sub = [&]() {
+    *reinterpret_cast<u32x4_t*>(xs + (tid >> 3) * XS + (tid & 7) * 16) = xr;
+#pragma unroll
+    for (int v = 0; v < ZV; ++v)
+      store_split8<NP>(zr[v], zs + (tid / G + v * ZR) * ZS + tid % G * 16, ZB);
+  };
+  f32x4_t accw[ET][2];
+#pragma unroll
+  for (int i = 0; i < ET; ++i) accw[i][0] = accw[i][1] = f32x4_t{};
+  const bool do_bias = a.part_b && (int)blockIdx.x < a.n_bparts;
+  float bacc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  load_sub(chunk * RB_CHUNK);
+  for (int sc = 0; sc < n_sub; ++sc) {
+    const int t0 = chunk * RB_CHUNK + sc * SUB;
+    __syncthreads();  // the previous sub-chunk's LDS reads are done
+    store_sub();
+    if (do_bias && sc % a.n_bparts == (int)blockIdx.x)
+#pragma unroll
+      for (int v = 0; v < ZV; ++v)
+#pragma unroll
+        for (int u = 0; u < 8; ++u) bacc[u] += zr[v][u];
+    __syncthreads();
+    if (sc + 1 < n_sub) load_sub(t0 + SUB);
+    const int t = t0 + quarter * 16 + l16;
+    bf16x4_t old[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int c = c0 + col0 + 16 * j + 4 * g4;
+      if (a.accumulate_dx && t < a.T && c < a.d)
+        old[j] = *reinterpret_cast<const bf16x4_t*>(dx + (size_t)t * a.d + c);
+    }
+#pragma unroll
+    for (int ks = 0; ks < SUB / 32; ++ks) {  // dW: k = tokens
+      bf16x8_t xf[2];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) xf[j] = frag_tr16(xs, XS, ks * 32, col0 + 16 * j);
+#pragma unroll
+      for (int i = 0; i < ET; ++i) {
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+          const bf16x8_t zf = frag_tr16(zs + p * ZB, ZS, ks * 32, quarter * EQ + 16 * i);
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+            accw[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf[j], zf, accw[i][j], 0, 0, 0);
+        }
+      }
+    }
+    f32x4_t accx[2] = {f32x4_t{}, f32x4_t{}};
+#pragma unroll
+    for (int ks = 0; ks < EP / 32; ++ks) {  // dx: k = experts
+      const char* zrow = zs + (quarter * 16 + l16) * ZS + (ks * 32 + 8 * g4) * 2;
+      bf16x8_t wf[2];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) wf[j] = frag_tr16(wl, XS, ks * 32, col0 + 16 * j);
+#pragma unroll
+      for (int p = 0; p < NP; ++p) {
+        const bf16x8_t zf = *reinterpret_cast<const bf16x8_t*>(zrow + p * ZB);
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          accx[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[j], zf, accx[j], 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int c = c0 + col0 + 16 * j + 4 * g4;
+      if (t >= a.T || c >= a.d) continue;
+      bf16x4_t o;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const float add = a.inv_tau * accx[j][u];
+        o[u] = (bf16_t)(a.accumulate_dx ? (float)old[j][u] + add : add);
+      }
+      *reinterpret_cast<bf16x4_t*>(dx + (size_t)t * a.d + c) = o;
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < ET; ++i) {
+    const int e = quarter * EQ + 16 * i + l16;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int c = c0 + col0 + 16 * j + 4 * g4;
+      if (e < a.E && c < a.d)
+        *reinterpret_cast<f32x4_t*>(a.part_w + ((size_t)chunk * a.E + e) * a.d + c) =
+            accw[i][j] * a.part_scale;
+    }
+  }
+  if (do_bias) {
+    __syncthreads();
+    float* rows = reinterpret_cast<float*>(zs);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) rows[tid / G * EP + tid % G * 8 + u] = bacc[u];
+    __syncthreads();
+    store_bias<EP, ZR>(a, chunk, rows);
+  }
+}
+
+// Router backward of fp32 layers on v_mfma_f32_16x16x4_f32: 4 waves, 64 columns
+// x RB_CHUNK tokens in sub-chunks of 64, EP (16, 64, 128 or 256) experts in LDS.
+// Wave w computes 16 columns of dW (MFMA tile i of expert block b: experts 64 b
+// + MI (l % 16) + i, so a lane reads MI consecutive ones) and of dx.  The VALU
+// kernels this replaces waited out a memory latency per 32 tokens: 256 tokens,
+// d = 64, 8 experts took 49 (dW) + 5 us (dx), now 10.
+template <int EP>
+__global__ __launch_bounds__(256) void route_bwd_f32_kernel(RouteBwdArgs a) {
+  constexpr int SUB = RBM_SUB, XS = RBW_COLS + 4, ZS = EP + 4;  // row strides (floats)
+  constexpr int MI = EP >= 64 ? 4 : 1, EB = EP / (16 * MI);
+  constexpr int G = EP / 4, ZR = 256 / G, ZV = SUB / ZR;  // dz: 4-expert groups, rows per pass, passes
+  __shared__ __attribute__((aligned(16))) float lds[SUB * XS + SUB * ZS + EP * XS];
+  float* xs = lds;
+  float* zs = xs + SUB * XS;
+  float* wl = zs + SUB * ZS;
+  static_assert(ZR * EP <= SUB * XS, "the bias shares fit over x");
+  const float* x = static_cast<const float*>(a.x);
+  const float* w = static_cast<const float*>(a.w);
+  float* dx = static_cast<float*>(a.dx);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l16 = lane & 15, g4 = lane >> 4;
+  const int c0 = blockIdx.x * RBW_COLS, chunk = blockIdx.y;
+  const int n_sub = (min(RB_CHUNK, a.T - chunk * RB_CHUNK) + SUB - 1) / SUB;
+  const bool vec_dz = (a.E & 3) == 0 && ((uintptr_t)a.dz & 15) == 0;
+  const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+  const int col = c0 + (tid & 15) * 4;  // this thread's columns of x and W_r
+  f32x4_t xr[4];
+  float zr[ZV][4];
+  auto load_sub = [&](int t0) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int t = t0 + (tid >> 4) + 16 * v;
+      xr[v] = t < a.T && col < a.d ? *reinterpret_cast<const f32x4_t*>(x + (size_t)t * a.d + col) : zero;
+    }
+#pragma unroll
+    for (int v = 0; v < ZV; ++v) load_dz<4>(a, t0 + tid / G + v * ZR, tid % G * 4, vec_dz, zr[v]);
+  };
+  load_sub(chunk * RB_CHUNK);
+#pragma unroll 4
+  for (int e = tid >> 4; e < EP; e += 16)
+    *reinterpret_cast<f32x4_t*>(wl + e * XS + (tid & 15) * 4) =
+        e < a.E && col < a.d ? *reinterpret_cast<const f32x4_t*>(w + (size_t)e * a.d + col) : zero;
+  f32x4_t accw[EB][MI];
+#pragma unroll
+  for (int b = 0; b < EB; ++b)
+#pragma unroll
+    for (int i = 0; i < MI; ++i) accw[b][i] = zero;
+  const bool do_bias = a.part_b && (int)blockIdx.x < a.n_bparts;
+  f32x4_t bacc = zero;
+  const int oc = c0 + wave * 16 + 4 * g4;  // the lane's 4 output columns
+  for (int sc = 0; sc < n_sub; ++sc) {
+    const int t0 = chunk * RB_CHUNK + sc * SUB;
+    __syncthreads();  // the previous sub-chunk's LDS reads are done
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      *reinterpret_cast<f32x4_t*>(xs + ((tid >> 4) + 16 * v) * XS + (tid & 15) * 4) = xr[v];
+#pragma unroll
+    for (int v = 0; v < ZV; ++v) {
+      const f32x4_t z = {zr[v][0], zr[v][1], zr[v][2], zr[v][3]};
+      *reinterpret_cast<f32x4_t*>(zs + (tid / G + v * ZR) * ZS + tid % G * 4) = z;
+      if (do_bias && sc % a.n_bparts == (int)blockIdx.x) bacc += z;
+    }
+    __syncthreads();
+    if (sc + 1 < n_sub) load_sub(t0 + SUB);
+    f32x4_t old[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int t = t0 + 16 * i + l16;
+      if (a.accumulate_dx && t < a.T && oc < a.d)
+        old[i] = *reinterpret_cast<const f32x4_t*>(dx + (size_t)t * a.d + oc);
+    }
+#pragma unroll 4
+    for (int s = 0; s < SUB / 4; ++s) {  // dW: k = tokens
+      const int k = 4 * s + g4;
+      const float xv = xs[k * XS + wave * 16 + l16];
+#pragma unroll
+      for (int b = 0; b < EB; ++b) {
+        typedef __attribute__((__vector_size__(MI * 4))) float vM;
+        const vM zv = *reinterpret_cast<const vM*>(zs + k * ZS + 64 * b + MI * l16);
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+          accw[b][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv, zv[i], accw[b][i], 0, 0, 0);
+      }
+    }
+    f32x4_t accx[4] = {zero, zero, zero, zero};
+#pragma unroll 2
+    for (int q = 0; q < EP / 16; ++q) {  // dx: k = experts
+      f32x4_t zv[4];
+      float wv[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        zv[i] = *reinterpret_cast<const f32x4_t*>(zs + (16 * i + l16) * ZS + 16 * q + 4 * g4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) wv[e] = wl[(16 * q + 4 * g4 + e) * XS + wave * 16 + l16];
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          accx[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[e], zv[i][e], accx[i], 0, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int t = t0 + 16 * i + l16;
+      if (t >= a.T || oc >= a.d) continue;
+      f32x4_t v = accx[i] * a.inv_tau;
+      if (a.accumulate_dx) v += old[i];
+      *reinterpret_cast<f32x4_t*>(dx + (size_t)t * a.d + oc) = v;
+    }
+  }
+#pragma unroll
+  for (int b = 0; b < EB; ++b)
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+      const int e = 64 * b + MI * l16 + i;
+      if (e < a.E && oc < a.d)
+        *reinterpret_cast<f32x4_t*>(a.part_w + ((size_t)chunk * a.E + e) * a.d + oc) =
+            accw[b][i] * a.part_scale;
+    }
+  if (do_bias) {
+    __syncthreads();
+    *reinterpret_cast<f32x4_t*>(xs + tid / G * EP + tid % G * 4) = bacc;
+    __syncthreads();
+    store_bias<EP, ZR>(a, chunk, xs);
   }
 }
 
@@ -951,38 +1272,45 @@ hipError_t launch_route_fwd(const void* x, const void* w, const float* bias, int
   if (T == 0) return hipSuccess;
   const dim3 grid(ceil_div(T, RT_TOK));
   const int neb = E <= 32 ? 1 : E <= 64 ? 2 : E <= 128 ? 4 : 8;
-  // slices of d per wave for the staged bf16 path (0: not taken)
-  const int xs = (!bf16 || neb > 2) ? 0 : d <= 64 * 4 * RT_WAVES ? 4 : d <= 64 * 8 * RT_WAVES ? 8 : 0;
-#define ROUTE_LAUNCH(N, B, X) \
-  MOE_TIMED("route_fwd", s, route_fwd_kernel<N, B, X><<<grid, RT_THREADS, 0, s>>>(a))
+  const bool vec = d % 4 == 0 && ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(w)) & 15) == 0;
+#define ROUTE_LAUNCH(N, P) MOE_TIMED("route_fwd", s, route_fwd_kernel<N, P><<<grid, RT_THREADS, 0, s>>>(a))
+#define ROUTE_F32(N)                       \
+  do {                                     \
+    if (vec) ROUTE_LAUNCH(N, RING_F32);    \
+    else ROUTE_LAUNCH(N, RING_F32_DWORD);  \
+  } while (0)
+#define ROUTE_BF16(N)                                        \
+  do {                                                       \
+    if (d <= 64 * 4 * RT_WAVES) ROUTE_LAUNCH(N, STAGED4);    \
+    else if (d <= 64 * 8 * RT_WAVES) ROUTE_LAUNCH(N, STAGED8); \
+    else ROUTE_LAUNCH(N, DIRECT);                            \
+  } while (0)
   switch (neb) {
     case 1:
-      if (xs == 4) ROUTE_LAUNCH(1, true, 4);
-      else if (xs == 8) ROUTE_LAUNCH(1, true, 8);
-      else if (bf16) ROUTE_LAUNCH(1, true, 0);
-      else ROUTE_LAUNCH(1, false, 0);
+      if (bf16) ROUTE_BF16(1);
+      else ROUTE_F32(1);
       break;
     case 2:
-      if (xs == 4) ROUTE_LAUNCH(2, true, 4);
-      else if (xs == 8) ROUTE_LAUNCH(2, true, 8);
-      else if (bf16) ROUTE_LAUNCH(2, true, 0);
-      else ROUTE_LAUNCH(2, false, 0);
+      if (bf16) ROUTE_BF16(2);
+      else ROUTE_F32(2);
       break;
     case 4:
-      if (bf16) ROUTE_LAUNCH(4, true, 0);
-      else ROUTE_LAUNCH(4, false, 0);
+      if (bf16) ROUTE_LAUNCH(4, RING);
+      else ROUTE_F32(4);
       break;
     default:
-      if (bf16) ROUTE_LAUNCH(8, true, 0);
-      else ROUTE_LAUNCH(8, false, 0);
+      if (bf16) ROUTE_LAUNCH(8, RING);
+      else ROUTE_F32(8);
       break;
   }
 #undef ROUTE_LAUNCH
+#undef ROUTE_F32
+#undef ROUTE_BF16
   return hipGetLastError();
 }
 
-// d_bias partial sums per chunk: one per 64-token sub-chunk in the MFMA
-// kernel (at most one per column block), one in the VALU kernels
+// d_bias partial sums per chunk: one per 64-token sub-chunk (at most one per 128
+// columns)
 int route_bwd_bparts(int d) { return std::max(1, std::min(d / RBM_COLS, RB_CHUNK / RBM_SUB)); }
 
 size_t route_bwd_ws_bytes(int T, int d, int E) {
@@ -996,31 +1324,42 @@ hipError_t launch_route_bwd(const void* x, const void* w, int bf16, int T, int d
                             float* d_bias, void* dx, int accumulate_dx, void* ws,
                             hipStream_t s) {
   const int n_chunks = (T + RB_CHUNK - 1) / RB_CHUNK;
-  float* part_w = static_cast<float*>(ws);
-  float* part_b = part_w + (size_t)n_chunks * E * d;
-  const bool mfma = bf16 && E <= 64 && d % RBM_COLS == 0;
+  const bool dw_vec = (reinterpret_cast<uintptr_t>(dw_router) & 15) == 0;
+  // a single chunk's sums are the results: no partials, no reduction
+  const bool direct = n_chunks == 1 && dw_vec;
+  float* part_w = direct ? dw_router : static_cast<float*>(ws);
+  float* part_b = !d_bias ? nullptr : direct ? d_bias : part_w + (size_t)n_chunks * E * d;
   RouteBwdArgs a{x, w, idx, tw, logits, dtw, dz, dw_router, d_bias, dx, part_w, part_b,
-                 T, d, E, k, gate, accumulate_dx, n_chunks,
-                 mfma ? std::min(d / RBM_COLS, RB_CHUNK / RBM_SUB) : 1, inv_tau};
-  if (T > 0) MOE_TIMED("route_dz", s, route_dz_kernel<<<ceil_div(T, 4), 256, 0, s>>>(a));
-  if (n_chunks > 0) {
-    if (mfma) {
-      const dim3 g(d / RBM_COLS, n_chunks);
-      MOE_TIMED("route_bwd_mfma", s, route_bwd_mfma_kernel<<<g, 256, 0, s>>>(a));
+                 T, d, E, k, gate, accumulate_dx, n_chunks, direct ? 1 : route_bwd_bparts(d),
+                 inv_tau, direct ? inv_tau : 1.f};
+  if (T > 0) {
+    MOE_TIMED("route_dz", s, route_dz_kernel<<<ceil_div(T, 4), 256, 0, s>>>(a));
+    const dim3 g128(ceil_div(d, RBM_COLS), n_chunks), g64(ceil_div(d, RBW_COLS), n_chunks);
+    if (bf16) {
+      if (E <= 64 && d % RBM_COLS == 0)
+        MOE_TIMED("route_bwd_mfma", s, route_bwd_mfma_kernel<2><<<g128, 256, 0, s>>>(a));
+      else if (E <= 64) MOE_TIMED("route_bwd_mfma", s, route_bwd_mfma_kernel<3><<<g128, 256, 0, s>>>(a));
+      else if (E <= 128) MOE_TIMED("route_bwd_wide", s, route_bwd_wide_kernel<128><<<g64, 512, 0, s>>>(a));
+      else MOE_TIMED("route_bwd_wide", s, route_bwd_wide_kernel<256><<<g64, 512, 0, s>>>(a));
     } else {
-      const dim3 g(ceil_div(d, 64), ceil_div(E, 64), n_chunks);
-      if (bf16) MOE_TIMED("route_dw_partial", s, route_dw_partial_kernel<bf16_t><<<g, 256, 0, s>>>(a));
-      else MOE_TIMED("route_dw_partial", s, route_dw_partial_kernel<float><<<g, 256, 0, s>>>(a));
+      if (E <= 16) MOE_TIMED("route_bwd_f32", s, route_bwd_f32_kernel<16><<<g64, 256, 0, s>>>(a));
+      else if (E <= 64) MOE_TIMED("route_bwd_f32", s, route_bwd_f32_kernel<64><<<g64, 256, 0, s>>>(a));
+      else if (E <= 128) MOE_TIMED("route_bwd_f32", s, route_bwd_f32_kernel<128><<<g64, 256, 0, s>>>(a));
+      else MOE_TIMED("route_bwd_f32", s, route_bwd_f32_kernel<256><<<g64, 256, 0, s>>>(a));
     }
   }
-  {
-    // n_chunks == 0 (T == 0) sums nothing and writes zeros
-    const int blocks = (int)std::min<size_t>(4096, ((size_t)E * d + 255) / 256);
-    MOE_TIMED("route_dw_reduce", s, route_dw_reduce_kernel<<<blocks, 256, 0, s>>>(a));
-  }
-  if (T > 0 && !mfma) {
-    if (bf16) MOE_TIMED("route_dx", s, route_dx_kernel<bf16_t><<<ceil_div(T, 8), 256, 0, s>>>(a));
-    else MOE_TIMED("route_dx", s, route_dx_kernel<float><<<ceil_div(T, 8), 256, 0, s>>>(a));
+  if (!direct) {
+    // n_chunks == 0 (T == 0) sums nothing and writes zeros.  16 bytes per
+    // access once that still gives every CU a block (256 experts x 1536: 12.3
+    // us with 4-byte accesses).
+    const size_t n = (size_t)E * d;
+    if (dw_vec && n >= (size_t)4 * 256 * 256) {
+      const int blocks = (int)std::min<size_t>(4096, (n / 4 + 255) / 256);
+      MOE_TIMED("route_dw_reduce", s, route_dw_reduce_kernel<4><<<blocks, 256, 0, s>>>(a));
+    } else {
+      const int blocks = (int)std::min<size_t>(4096, (n + 255) / 256);
+      MOE_TIMED("route_dw_reduce", s, route_dw_reduce_kernel<1><<<blocks, 256, 0, s>>>(a));
+    }
   }
   return hipGetLastError();
 }

@@ -54,9 +54,9 @@ _SYMBOLS = [
     (r"route_fwd_kernel", lambda m: "route_fwd"),
     (r"route_dz_kernel", lambda m: "route_dz"),
     (r"route_bwd_mfma_kernel", lambda m: "route_bwd_mfma"),
-    (r"route_dw_partial_kernel", lambda m: "route_dw_partial"),
+    (r"route_bwd_wide_kernel", lambda m: "route_bwd_wide"),
+    (r"route_bwd_f32_kernel", lambda m: "route_bwd_f32"),
     (r"route_dw_reduce_kernel", lambda m: "route_dw_reduce"),
-    (r"route_dx_kernel", lambda m: "route_dx"),
     (r"dispatch_count_kernel", lambda m: "dispatch_count"),
     (r"dispatch_scan_kernel", lambda m: "dispatch_scan"),
     (r"dispatch_scatter_kernel", lambda m: "dispatch_scatter"),
