@@ -76,8 +76,8 @@ DEVI int gu_brow(int tile_n, int c, int H, bool& ok) {
 // barrier after which stage kt is free, and refills it with k-step kt+NS (if
 // the tile has one).
 //
-// Tile order (see tile_decode): bands of GROUP_M m-tiles (2 to 8, per kind,
-// see Cfg).  Each XCD takes an equal share of every set's tile range (blocks
+// Tile order (see tile_decode): in bands of m-tiles (Cfg::BAND).
+// Each XCD takes an equal share of every set's tile range (blocks
 // are placed on the 8 XCDs round-robin by id): the 32 tiles an XCD runs at a
 // time form a band rectangle whose operand panels its L2 serves.  With
 // counters the blocks of an XCD take its tiles one at a time.  Output tiles
@@ -141,9 +141,16 @@ struct Cfg {
   static constexpr int DMA_N = DMA_A + DMA_B;
   static constexpr int DMA_MAX = DMA_A > DMA_B ? DMA_A : DMA_B;
   static constexpr int EPI_WAVE = WM * 256;        // epilogue staging per wave
-  // m-tiles per band of the tile order, measured per kind on the
-  // fine-grained workload (bands of 1, 2, 4, 8 and 16 tried)
-  static constexpr int GROUP = KIND == DOWN_FWD || KIND == DX_BWD ? 8 : 2;
+  // Tile order: bands of BAND m-tiles.  The forward kinds walk group by group,
+  // in bands of equal height: the 32 tiles that an XCD runs at a time then span
+  // about 6 x 5 (4 x 8) tiles of one expert's weights.  (Bands that ran across
+  // groups had to be 2 high for GU: large workload, GU 2004 -> 1927 us, down
+  // projection 1050 -> 1014; fine-grained down projection 165 -> 159, GU level.)
+  // The other kinds' bands run across the groups: by group their merged
+  // launches were 1 % slower (the longer decode spills there).
+  static constexpr bool BY_GROUP = Kind<KIND>::B_KC;
+  static constexpr int BAND = KIND == GU_FWD || KIND == UP_FWD ? 6 : KIND == DOWN_FWD ? 4
+                              : KIND == DX_BWD ? 8 : 2;
   static_assert(NW * EPI_WAVE <= LDS, "epilogue staging exceeds the ring");
 };
 
@@ -318,13 +325,6 @@ DEVI float sigmoid_fast(float g) {
 }
 DEVI float silu_fast(float g) { return g * sigmoid_fast(g); }
 
-// Tile enumeration.  Output tiles form an m_tiles x n_tiles grid (M-ragged
-// kinds: m-tiles of all groups in group order; K-ragged kinds: (group,
-// m-tile) pairs).  Linear tile t walks bands of GROUP_M m-tiles: inside a band
-// m varies fastest, then n, so any 32 consecutive tiles cover a GROUP_M x
-// (32 / GROUP_M) rectangle and share GROUP_M A panels and 32 / GROUP_M B
-// panels in L2.
-
 // Output tiles form an m_tiles x n_tiles grid (M-ragged kinds: m-tiles of all
 // groups in group order; K-ragged kinds: (group, split part, m-tile)
 // triples).
@@ -338,39 +338,60 @@ DEVI int m_tile_count(const GemmArgs& a, const GroupTable& t) {
   }
 }
 
-// Linear tile t walks bands of GROUP_M m-tiles: inside a band m varies
-// fastest, then n, so any 32 consecutive tiles cover a GROUP_M x
-// (32 / GROUP_M) rectangle and share GROUP_M A panels and 32 / GROUP_M B
-// panels in L2.  The m-tile's group is found by all lanes of the wave at once
-// (the number of groups whose m-tiles all lie before it).
+// Linear tile t walks bands of BAND m-tiles (Cfg): inside a band m varies
+// fastest, then n, so consecutive tiles share their panels in L2.  The m-tile's
+// group is found by all lanes of the wave at once (the number of groups whose
+// m-tiles all lie before it).
 // M-ragged kinds cut into `parts` K parts: m_tiles counts (m-tile, part)
 // pairs, part fastest.
 template <int KIND>
 DEVI void tile_decode(const GemmArgs& a, const GroupTable& gt, int t, int m_tiles, int n_tiles,
                       int parts, Tile& tl, int& tile_n) {
-  constexpr int BM = Cfg<KIND>::BM, GROUP_M = Cfg<KIND>::GROUP;
-  const int band = t / (GROUP_M * n_tiles);
-  const int first_m = band * GROUP_M;
-  const int band_m = min(GROUP_M, m_tiles - first_m);
-  const int r = t - band * GROUP_M * n_tiles;
-  int q = first_m + r % band_m;  // m-tile (and part)
-  tile_n = r / band_m;
-  tl.n0 = tile_n * GT;
-  if constexpr (Kind<KIND>::MRAG) {
-    const int part = q % parts;
-    q /= parts;
+  constexpr int BM = Cfg<KIND>::BM, BAND = Cfg<KIND>::BAND;
+  // group of (m-tile, part) pair q
+  auto group_of = [&](int q) {
     const int lane = threadIdx.x & 63;
     int g = 0;
     for (int g0 = 0; g0 < a.n_groups; g0 += 64) {
       const int gg = g0 + lane;
-      g += __builtin_popcountll(__ballot(gg < a.n_groups && gt.p[gg + 1] <= q));
+      g += __builtin_popcountll(__ballot(gg < a.n_groups && gt.p[gg + 1] * parts <= q));
     }
-    g = __builtin_amdgcn_readfirstlane(g);
+    return __builtin_amdgcn_readfirstlane(g);
+  };
+  if constexpr (Cfg<KIND>::BY_GROUP) {
+    const int g = group_of(t / n_tiles);
+    const int first = __builtin_amdgcn_readfirstlane(gt.p[g]) * parts;
+    const int M = __builtin_amdgcn_readfirstlane(gt.p[g + 1]) * parts - first;
+    int r = t - first * n_tiles;
+    const int bands = (M + BAND - 1) / BAND;
+    const int h = (M + bands - 1) / bands;
+    const int b = r / (h * n_tiles);
+    r -= b * h * n_tiles;
+    const int bm = min(h, M - b * h);
+    const int q = b * h + r % bm;  // (m-tile, part) of the group
+    tile_n = r / bm;
+    tl.n0 = tile_n * GT;
     tl.g = g;
-    tl.row0 = gt.b[g] + (q - gt.p[g]) * BM;
+    tl.row0 = gt.b[g] + q / parts * BM;
     tl.rows = min(BM, gt.b[g + 1] - tl.row0);
     tl.m0 = 0;
-    tl.split = part;
+    tl.split = q % parts;
+    return;
+  }
+  const int band = t / (BAND * n_tiles);
+  const int first_m = band * BAND;
+  const int band_m = min(BAND, m_tiles - first_m);
+  const int r = t - band * BAND * n_tiles;
+  int q = first_m + r % band_m;  // m-tile (and part)
+  tile_n = r / band_m;
+  tl.n0 = tile_n * GT;
+  if constexpr (Kind<KIND>::MRAG) {
+    const int g = group_of(q);
+    tl.g = g;
+    tl.row0 = gt.b[g] + (q / parts - gt.p[g]) * BM;
+    tl.rows = min(BM, gt.b[g + 1] - tl.row0);
+    tl.m0 = 0;
+    tl.split = q % parts;
   } else {
     // (group, split part, m-tile); part p of a group of rows [b, e) is
     // [b + len p / S, b + len (p + 1) / S)
