@@ -148,6 +148,8 @@ def algorithmic_work(cfg, n, t_act, s, expert="swiglu"):
     w["route_bwd_mfma"] = ("byte", T * E * 4 + 3 * T * d * s + E * d * s
                            + -(-T // 256) * E * d * 4)
     w["route_bwd_wide"] = w["route_bwd_f32"] = w["route_bwd_mfma"]
+    # the same GEMM launches in small tiles
+    w.update({f"{name}_tile": v for name, v in w.items() if name.startswith("gemm_")})
     return w
 
 

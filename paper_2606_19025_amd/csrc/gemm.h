@@ -1,4 +1,5 @@
-// Shared by the grouped-GEMM kernels (bf16: gemm.hip, fp32: gemm_f32.hip): the
+// Shared by the grouped-GEMM kernels (large bf16 tiles: gemm.hip, the others:
+// gemm_tile.hip): the
 // GEMM kinds, their arguments, the group table and the launch record.
 #pragma once
 #include <type_traits>
@@ -113,23 +114,24 @@ struct GemmLaunch {
   int* counters;  // non-null: per-XCD tile counters (zero at launch) for dynamic dealing
 };
 
-constexpr const char* kGemmNames[] = {"gemm_gu_fwd", "gemm_down_fwd", "gemm_dhh_bwd",
-                                      "gemm_dx_bwd", "gemm_dwd", "gemm_dwgu",
-                                      "gemm_up_fwd", "gemm_dh_bwd"};
-
-template <int KA, int KB>
-const char* gemm_name() {
-  if constexpr (KA == KB) return kGemmNames[KA];
-  else if constexpr (KA == DHH_BWD && KB == DWD) return "gemm_dhh_dwd";
-  else if constexpr (KA == DH_BWD && KB == DWD) return "gemm_dh_dwd";
-  else if constexpr (KA == DX_BWD && KB == DWGU) return "gemm_dx_dwgu";
-  else return "gemm_merged";
+// Timing names of the launches; the small tiles' end in _tile.
+#define MOE_GEMM_NAMES(S)                                                                     \
+  {"gemm_gu_fwd" S, "gemm_down_fwd" S, "gemm_dhh_bwd" S, "gemm_dx_bwd" S, "gemm_dwd" S,       \
+   "gemm_dwgu" S, "gemm_up_fwd" S, "gemm_dh_bwd" S, "gemm_dhh_dwd" S, "gemm_dh_dwd" S,        \
+   "gemm_dx_dwgu" S}
+constexpr const char* kGemmNames[] = MOE_GEMM_NAMES("");
+constexpr const char* kTileNames[] = MOE_GEMM_NAMES("_tile");
+constexpr int gemm_name_index(int ka, int kb) {
+  return ka == kb ? ka : ka == DHH_BWD ? 8 : ka == DH_BWD ? 9 : 10;
 }
 
-// fp32: one launch over sets_a[0..na) of kind ka and sets_b[0..nb) of kind kb
-// (kb == ka with nb = 0: one kind).
-hipError_t run_gemm_f32(int ka, int kb, const GemmArgs* sets_a, int na, const GemmArgs* sets_b,
-                        int nb, hipStream_t s);
+// Output tiles of the bf16 launches (fp32 ones choose by themselves).  TILE_32x64:
+// launches of one kind only.
+enum TileSize { TILE_256x256, TILE_64x128, TILE_64x64, TILE_32x64 };
+// The small tiles (gemm_tile.hip): one launch over sets_a[0..na) of kind ka and
+// sets_b[0..nb) of kind kb (kb == ka with nb = 0: one kind).
+hipError_t run_gemm_tile(int bf16, int ka, int kb, const GemmArgs* sets_a, int na,
+                         const GemmArgs* sets_b, int nb, TileSize size, hipStream_t s);
 
 int num_cus();
 

@@ -22,7 +22,10 @@
 // global -> LDS DMA (details at gemm_bf16_kernel and Cfg).  One launch
 // covers up to two expert sets (routed and shared experts) of one kind, or
 // in the backward two independent kinds (dHh with dW_d, dX with dW_gu).
-// fp32: gemm_f32.hip.
+// Launches too small for these tiles, and fp32 layers: gemm_tile.hip
+// (choose_tiles).
+#include <cmath>
+
 #include "gemm.h"
 #include "kernels.h"
 #include "timing.h"
@@ -178,7 +181,7 @@ DEVI void store16(__amdgpu_buffer_rsrc_t r, unsigned off, u32x4_t v) {
 // later LDS read as possibly aliasing the pending DMA (it would wait for all
 // outstanding global loads before each transposing read); the kernel waits for
 // the DMA explicitly (vmcnt) before the barrier that publishes a stage.  The
-// asm sets m0 itself; the compiler keeps no value of its own in m0 across it
+// asm sets m0 itself (and leaves the one wait state an LDS DMA needs after it); the compiler keeps no value of its own in m0 across it
 // (m0 is reserved, and nothing else in these kernels uses it), which the
 // "m0" clobber records for the reader.
 DEVI void load_to_lds(u32x4_t rsrc, unsigned off, char* lds_base) {
@@ -187,7 +190,7 @@ DEVI void load_to_lds(u32x4_t rsrc, unsigned off, char* lds_base) {
   // tile context has passed through registers the compiler treats as per-lane
 #pragma unroll
   for (int w = 0; w < 4; ++w) rsrc[w] = __builtin_amdgcn_readfirstlane(rsrc[w]);
-  asm volatile("s_mov_b32 m0, %2\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(off), "s"(rsrc), "s"(m0)
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(off), "s"(rsrc), "s"(m0)
                : "m0", "memory");
 }
 // Raw buffer resource over [base, base + kOOB): stride 0, no swizzle, word 3
@@ -1095,15 +1098,8 @@ hipError_t run_gemm_bf16(const GemmArgs* sets_a, int na, const GemmArgs* sets_b,
   // persistent: at most one block per CU, a multiple of N_XCD blocks
   long blocks = std::min<long>((long)num_cus(), tiles);
   blocks = std::max<long>(N_XCD, (blocks + N_XCD - 1) / N_XCD * N_XCD);
-  MOE_TIMED((gemm_name<KA, KB>()), s, gemm_bf16_kernel<KA, KB><<<(int)blocks, 512, 0, s>>>(L));
+  MOE_TIMED((kGemmNames[gemm_name_index(KA, KB)]), s, gemm_bf16_kernel<KA, KB><<<(int)blocks, 512, 0, s>>>(L));
   return hipGetLastError();
-}
-
-// One launch per set group of one GEMM kind.
-template <int KIND>
-hipError_t run_gemm(const GemmArgs* sets, int n_sets, int bf16, hipStream_t s) {
-  if (bf16) return run_gemm_bf16<KIND, KIND>(sets, n_sets, nullptr, 0, s, nullptr);
-  return run_gemm_f32(KIND, KIND, sets, n_sets, nullptr, 0, s);
 }
 
 // counters[0..n) = 0 (the per-XCD tile counters of the next launches)
@@ -1268,6 +1264,74 @@ hipError_t reduce_row_parts(const GemmArgs* args, int n_sets, hipStream_t s) {
   return hipSuccess;
 }
 
+// Which tiles a bf16 launch takes: the smallest estimate of its time.  256 x 256
+// tiles need the fewest operand bytes and run at the highest rate once they
+// fill the CUs; with few, ragged or short ones most CUs idle or each tile's
+// fill and epilogue weigh more than its k-steps, and smaller tiles (two or three
+// blocks per CU) finish earlier.  The sizes are known to the host only by
+// their bound; of a set with several groups, 0.6 of it is taken as present
+// (skip-token leaves 0.2 to 1 of the routes resident).
+// The constants are fits (us per 64-deep k-step and per tile, of a whole CU and
+// of a lone block) to the launches of twelve layers and expert blocks of 69 to
+// 16000 rows, d 64 to 2752, H 64 to 2816.  Measured, 256 x 256 / 64 x 128 / 64 x
+// 64: GU of 4096 rows, d = 1024, H = 2816, 8 groups: 76 / 103 / 130; its down
+// projection 48 + 10 (K parts and their sum) / 58 / 65; 2300 rows in 7 groups,
+// d = 960, H = 512: dX + dW 55 + 9 / 40 / 50; 300 rows, d = 1024, H = 1408, 4
+// groups: GU 30 / 19 / 17, dX + dW 37 + 7 / 38 / 31; the backward of a shared
+// expert of 6662 rows, H = 1152 beside 7 groups: dHh + dW_d 174 / 134 / 168 (its
+// dW_d tiles are few and long).
+struct TileCost {
+  int bm, bn;
+  double step, tile;            // of a CU's time
+  double lone_step, lone_tile;  // alone on a CU
+};
+constexpr TileCost kTileCost[] = {{256, 256, 1.45, 6.0, 1.45, 6.0},
+                                  {64, 128, 0.35, 1.6, 0.55, 6.0},
+                                  {64, 64, 0.25, 1.1, 0.45, 5.0}};
+
+double launch_us(const TileCost& c, int ka, const GemmArgs* sa, int na, const GemmArgs* sb, int nb,
+                 bool parts) {
+  double sum = 0, longest = 0, most_parts = 0;
+  for (int q = 0; q < na + nb; ++q) {
+    const GemmArgs& a = q < na ? sa[q] : sb[q - na];
+    if (a.n_groups == 0 || a.cap == 0) continue;
+    const bool mrag = q < na;  // every second kind of a launch is ragged in K
+    const double rows = a.n_groups == 1 ? a.cap : 0.6 * a.cap / a.n_groups;  // per group
+    double m = mrag ? rows / c.bm : (double)ceil_div(a.M, c.bm);
+    if (mrag) m = a.n_groups == 1 ? std::ceil(m) : std::max(1.0, m + 0.5);
+    const double tiles = m * a.n_groups * ceil_div(a.N, c.bn);
+    const double steps = std::ceil((mrag ? a.K : rows) / 64.0);
+    sum += tiles * (steps * c.step + c.tile);
+    const double lone = steps * c.lone_step + c.lone_tile;
+    // K parts cut the long tiles of the linear kinds
+    if (parts && mrag && (ka == DOWN_FWD || ka == DX_BWD)) most_parts = std::max(most_parts, lone);
+    else longest = std::max(longest, lone);
+  }
+  sum /= num_cus();
+  const double t = std::max(longest, sum + 0.3 * longest);
+  if (most_parts <= sum * 4 / 3) return std::max(t, most_parts);
+  return std::max(t, sum * 4 / 3) + 20;  // partial rows, their sum and its launch
+}
+
+TileSize choose_tiles(int ka, const GemmArgs* sa, int na, const GemmArgs* sb, int nb, bool parts) {
+  // about 32 rows per group or fewer: the weights' stream is all, with the
+  // deepest ring (48 tokens over the fine-grained experts: GU 51, down projection
+  // 29 us against 53 and 32 with 64 x 64 tiles, 57 and 49 + 5 with 256 x 256;
+  // 58 rows per group: 542 us against 396 with 64 x 128, two of whose rows of
+  // tiles would read each weight again)
+  if (nb == 0) {
+    bool few = true;
+    for (int q = 0; q < na; ++q)
+      few = few && (sa[q].n_groups == 1 ? sa[q].cap <= 64 : 0.6 * sa[q].cap <= 32.0 * sa[q].n_groups);
+    if (few) return TILE_32x64;
+  }
+  const double big = launch_us(kTileCost[0], ka, sa, na, sb, nb, parts);
+  const double mid = launch_us(kTileCost[1], ka, sa, na, sb, nb, false);
+  const double small = launch_us(kTileCost[2], ka, sa, na, sb, nb, false);
+  if (big <= mid && big <= small) return TILE_256x256;
+  return mid <= small ? TILE_64x128 : TILE_64x64;
+}
+
 }  // namespace
 
 // Rows of an expert's first weight per hidden unit: 2 (gate and up) for
@@ -1313,11 +1377,21 @@ hipError_t launch_ffn_fwd_sets(const moe_ffn_set* sets, int n_sets, int bf16, in
     b.C = f.yp; b.ldc = d;
     b.N = d; b.K = f.H;
   }
-  if (bf16) assign_row_parts(o, sets, n_sets, bf16, d, static_cast<char*>(ws));
-  hipError_t e = silu ? run_gemm<UP_FWD>(g, n_sets, bf16, s) : run_gemm<GU_FWD>(g, n_sets, bf16, s);
+  const int first = silu ? UP_FWD : GU_FWD;
+  TileSize size = bf16 ? choose_tiles(first, g, n_sets, nullptr, 0, false) : TILE_64x128;
+  hipError_t e;
+  if (bf16 && size == TILE_256x256)
+    e = silu ? run_gemm_bf16<UP_FWD, UP_FWD>(g, n_sets, nullptr, 0, s, nullptr)
+             : run_gemm_bf16<GU_FWD, GU_FWD>(g, n_sets, nullptr, 0, s, nullptr);
+  else
+    e = run_gemm_tile(bf16, first, first, g, n_sets, nullptr, 0, size, s);
   if (e != hipSuccess) return e;
-  if ((e = run_gemm<DOWN_FWD>(o, n_sets, bf16, s)) != hipSuccess) return e;
-  return reduce_row_parts(o, n_sets, s);
+  if (bf16) size = choose_tiles(DOWN_FWD, o, n_sets, nullptr, 0, ws != nullptr);
+  if (!bf16 || size != TILE_256x256)
+    return run_gemm_tile(bf16, DOWN_FWD, DOWN_FWD, o, n_sets, nullptr, 0, size, s);
+  assign_row_parts(o, sets, n_sets, bf16, d, static_cast<char*>(ws));
+  e = run_gemm_bf16<DOWN_FWD, DOWN_FWD>(o, n_sets, nullptr, 0, s, nullptr);
+  return e != hipSuccess ? e : reduce_row_parts(o, n_sets, s);
 }
 
 hipError_t launch_ffn_bwd_sets(const moe_ffn_set* sets, int n_sets, int bf16, int d,
@@ -1361,44 +1435,53 @@ hipError_t launch_ffn_bwd_sets(const moe_ffn_set* sets, int n_sets, int bf16, in
     w.B = f.xp; w.ldb = d;
     w.C = f.dw_gate_up; w.ldc = d; w.c_gs = R1 * H * d;
     w.M = (int)(R1 * f.H); w.N = d;
-    if (ws) {
-      for (GemmArgs* g : {&c, &w}) {
-        const int S = ksplit_factor(bf16, g->M, g->N, f,
-                                    bwd_launch_tiles(sets, n_sets, d, g == &w));
-        if (S <= 1) continue;
-        const size_t n = (size_t)g->M * g->N;
-        red[n_red++] = Reduce{static_cast<float*>(g->C), reinterpret_cast<const float*>(part), S, n};
-        g->C = part;
-        g->ksplit = S;
-        g->c_split = (long)n;
-        g->accumulate = 0;
-        part += align_up((size_t)S * n * sizeof(float));
-      }
+  }
+  // two launches of two independent kinds each: dHh with dW_d (both read dY),
+  // then dX with dW_gu (both read dG/dU)
+  TileSize size1 = TILE_64x128, size2 = TILE_64x128;
+  if (bf16) {
+    size1 = choose_tiles(silu ? DH_BWD : DHH_BWD, hh, n_sets, wd, n_sets, false);
+    size2 = choose_tiles(DX_BWD, dx, n_sets, wgu, n_sets, ws != nullptr);
+  }
+  const bool large1 = bf16 && size1 == TILE_256x256, large2 = bf16 && size2 == TILE_256x256;
+  // a single large group's dW split by rows, in the large tiles
+  for (int i = 0; ws && i < n_sets; ++i) {
+    for (GemmArgs* g : {&wd[i], &wgu[i]}) {
+      if (!(g == &wd[i] ? large1 : large2)) continue;
+      const int S = ksplit_factor(bf16, g->M, g->N, sets[i],
+                                  bwd_launch_tiles(sets, n_sets, d, g == &wgu[i]));
+      if (S <= 1) continue;
+      const size_t n = (size_t)g->M * g->N;
+      red[n_red++] = Reduce{static_cast<float*>(g->C), reinterpret_cast<const float*>(part), S, n};
+      g->C = part;
+      g->ksplit = S;
+      g->c_split = (long)n;
+      g->accumulate = 0;
+      part += align_up((size_t)S * n * sizeof(float));
     }
   }
-  if (bf16 && ws) assign_row_parts(dx, sets, n_sets, bf16, d, rows_ws);
   hipError_t e;
-  if (!bf16) {
-    // the same two launches as bf16
-    e = run_gemm_f32(silu ? DH_BWD : DHH_BWD, DWD, hh, n_sets, wd, n_sets, s);
-    if (e != hipSuccess) return e;
-    e = run_gemm_f32(DX_BWD, DWGU, dx, n_sets, wgu, n_sets, s);
-    if (e != hipSuccess) return e;
-  } else {
-    // two launches of two independent kinds each: dHh with dW_d (both read
-    // dY), then dX with dW_gu (both read dG/dU); with a workspace their tiles
-    // are dealt dynamically from per-XCD counters, cleared here first
-    if (ws) {
-      MOE_TIMED("zero_counters", s, zero_counters_kernel<<<1, 64, 0, s>>>(counters, kCounterWords));
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
+  // with a workspace the large tiles are dealt dynamically from per-XCD
+  // counters, cleared here first
+  if (ws && (large1 || large2)) {
+    MOE_TIMED("zero_counters", s, zero_counters_kernel<<<1, 64, 0, s>>>(counters, kCounterWords));
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  if (large1)
     e = silu ? run_gemm_bf16<DH_BWD, DWD>(hh, n_sets, wd, n_sets, s, ws ? counters : nullptr)
              : run_gemm_bf16<DHH_BWD, DWD>(hh, n_sets, wd, n_sets, s, ws ? counters : nullptr);
-    if (e != hipSuccess) return e;
+  else
+    e = run_gemm_tile(bf16, silu ? DH_BWD : DHH_BWD, DWD, hh, n_sets, wd, n_sets, size1, s);
+  if (e != hipSuccess) return e;
+  if (large2) {
+    if (ws) assign_row_parts(dx, sets, n_sets, bf16, d, rows_ws);
     e = run_gemm_bf16<DX_BWD, DWGU>(dx, n_sets, wgu, n_sets, s, ws ? counters + N_XCD : nullptr);
     if (e != hipSuccess) return e;
-    if ((e = reduce_row_parts(dx, n_sets, s)) != hipSuccess) return e;
+    e = reduce_row_parts(dx, n_sets, s);
+  } else {
+    e = run_gemm_tile(bf16, DX_BWD, DWGU, dx, n_sets, wgu, n_sets, size2, s);
   }
+  if (e != hipSuccess) return e;
   for (int r = 0; r < n_red; ++r) {
     const int blocks = (int)std::min<size_t>(8192, (red[r].n / 4 + 255) / 256);
     MOE_TIMED("splitk_reduce", s,

@@ -50,7 +50,8 @@ def _gemm_launch_name(ka: int, kb: int) -> str:
 _SYMBOLS = [
     (r"gemm_bf16_kernel(?:<|ILi)(\d)(?:, |ELi)(\d)", lambda m: _gemm_launch_name(int(m.group(1)), int(m.group(2)))),
     (r"gemm_bf16_kernel(?:<|ILi)(\d)", lambda m: GEMM_KINDS[int(m.group(1))]),
-    (r"gemm_f32_kernel(?:<|ILi)(\d)(?:, |ELi)(\d)", lambda m: _gemm_launch_name(int(m.group(1)), int(m.group(2)))),
+    (r"gemm_tile_kernel(?:<(?:[a-z_0-9]+, )?|I(?:f|DF16b)Li)(\d)(?:, |ELi)(\d)",
+     lambda m: _gemm_launch_name(int(m.group(1)), int(m.group(2))) + "_tile"),
     (r"route_fwd_kernel", lambda m: "route_fwd"),
     (r"route_dz_kernel", lambda m: "route_dz"),
     (r"route_bwd_mfma_kernel", lambda m: "route_bwd_mfma"),
@@ -106,11 +107,13 @@ def _code_only(src: str) -> str:
 
 def source_digest(name: str) -> str | None:
     """sha256 (16 hex digits) of the code of the kernel's source file and the
-    shared header (comments and layout ignored)."""
+    shared headers (comments and layout ignored)."""
     for prefix, fname in _SOURCES:
         if name.startswith(prefix):
             h = hashlib.sha256()
-            for f in (fname, "common.h"):
+            if name.endswith("_tile"):
+                fname = "gemm_tile.hip"
+            for f in (fname, "common.h") + (("gemm.h",) if fname.startswith("gemm") else ()):
                 with open(os.path.join(CSRC, f)) as fh:
                     h.update(_code_only(fh.read()).encode())
             return h.hexdigest()[:16]

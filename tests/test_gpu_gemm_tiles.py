@@ -1,0 +1,114 @@
+"""The bf16 grouped FFN in each of its tile sizes against the oracle.
+
+A launch takes 256 x 256, 64 x 128, 64 x 64 or 32 x 64 tiles by an estimate of
+its time.  The timing names tell the large tiles from the small ones; the
+shapes here reach every kind in both, with group sizes at the edges of the
+tile heights (empty, 1, 31..33, 63..65, 127..129, 255..257, 511, 513 rows),
+partial column tiles, ragged K of the weight gradients, both expert forms, one
+and two sets, with and without a workspace, and accumulated gradients.  The
+tolerance is the bf16 layers' own, normwise.
+"""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import moe_oracle as O
+from paper_2606_19025_amd import binding as B
+from paper_2606_19025_amd import inputs as I
+
+from .parity_helpers import TOL, assert_close, canary, host, record_errors, say
+
+pytestmark = pytest.mark.gpu
+
+F32 = torch.float32
+LARGE = [0, 1, 127, 128, 129, 0, 255, 256, 257, 383, 511, 513, 1300, 2001, 0]
+# name: (group sizes of each set, d, H of each set, expert, workspace, accumulate_dw, large launches)
+CASES = {
+    "all-large": ([LARGE], 2240, [1984], "swiglu", True, 1, "1111"),
+    "all-large-silu": ([LARGE], 2240, [1984], "silu", False, 0, "1111"),
+    "rows-32": ([[0, 1, 31, 32, 33, 2, 0]], 192, [320], "swiglu", True, 0, "0000"),
+    "rows-32-silu-shared": ([[7, 0, 30, 5], [42]], 128, [192, 448], "silu", False, 1, "0000"),
+    "rows-64": ([[63, 64, 65, 0, 127, 129, 1, 200]], 320, [704], "swiglu", True, 0, "0000"),
+    "rows-64-silu": ([[500, 3, 65, 0, 129]], 1088, [192], "silu", True, 1, "0000"),
+    "rows-64-shared": ([[260, 90, 0, 511], [861]], 448, [576, 1152], "swiglu", True, 0, "0000"),
+    "many-groups": ([[5 * (i % 17) for i in range(70)]], 64, [64], "swiglu", True, 0, "0000"),
+}
+
+
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_ffn_tile_sizes(gpu_lib, name):
+    set_sizes, d, Hs, expert, use_ws, acc, large = CASES[name]
+    say(f"[gemm-tiles] {name}")
+    g = np.random.default_rng([31, d, Hs[0]])
+    r1 = 2 if expert == "swiglu" else 1
+    act = B.ACTIVATIONS[expert]
+
+    def draw(*shape, std=1.0):
+        return I.bf16_round(g.standard_normal(shape, dtype=np.float32) * np.float32(std))
+
+    def dev(a, dt=torch.bfloat16):
+        return torch.from_numpy(a).cuda().to(dt)
+
+    sets, state = [], []
+    for sizes, H in zip(set_sizes, Hs):
+        G, n = len(sizes), sum(sizes)
+        cap = n + 70 if len(sizes) > 1 else n  # rows past the groups stay untouched
+        off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+        s = dict(sizes=sizes, H=H, n=n, off=off, xp=draw(cap, d), dyp=draw(cap, d),
+                 w1=draw(G, r1 * H, d, std=d ** -0.5), w2=draw(G, d, H, std=H ** -0.5))
+        for key, shape in (("dw1", (G, r1 * H, d)), ("dw2", (G, d, H))):
+            s[key] = (g.standard_normal(shape) * 0.01).astype(np.float32) if acc else None
+        t = {k: dev(s[k]) for k in ("xp", "dyp", "w1", "w2")}
+        t.update(off=torch.from_numpy(off).cuda(), gu=canary(cap, r1 * H), h=canary(cap, H),
+                 yp=canary(cap, d), dgu=canary(cap, r1 * H), dxp=canary(cap, d),
+                 dw1=dev(s["dw1"], F32) if acc else canary(G, r1 * H, d, dtype=F32),
+                 dw2=dev(s["dw2"], F32) if acc else canary(G, d, H, dtype=F32))
+        sets.append(B.ffn_set(t["xp"], t["w1"], t["w2"], t["off"], cap, H, G, t["gu"], t["h"],
+                              yp=t["yp"], dyp=t["dyp"], dgu=t["dgu"], dxp=t["dxp"],
+                              dw_gate_up=t["dw1"], dw_down=t["dw2"], activation=act))
+        state.append((s, t))
+    ws = {}
+    for way, size in (("fwd", B.moe_grouped_ffn_fwd_workspace_size),
+                      ("bwd", B.moe_grouped_ffn_bwd_workspace_size)):
+        n = size(sets, B.MOE_BF16, d) if use_ws else 0
+        ws[way] = (torch.full((n,), 0xFF, dtype=torch.uint8, device="cuda") if n else None, n)
+    B.moe_timing_enable(64)
+    try:
+        B.moe_grouped_ffn_fwd_sets(sets, B.MOE_BF16, d, *ws["fwd"])
+        B.moe_grouped_ffn_bwd_sets(sets, B.MOE_BF16, d, acc, *ws["bwd"])
+        ran = set(B.moe_timing_collect())
+    finally:
+        B.moe_timing_enable(0)
+    kinds = (("gemm_gu_fwd", "gemm_down_fwd", "gemm_dhh_dwd", "gemm_dx_dwgu") if expert == "swiglu"
+             else ("gemm_up_fwd", "gemm_down_fwd", "gemm_dh_dwd", "gemm_dx_dwgu"))
+    got = "".join("1" if k in ran else "0" for k in kinds)
+    assert all((k in ran) != (k + "_tile" in ran) for k in kinds), ran
+    assert got == large, f"large tiles in {got}, expected {large}"
+
+    tol, errs = TOL["bf16"], {}
+    for i, (s, t) in enumerate(state):
+        n, H = s["n"], s["H"]
+        f = O.grouped_ffn_fwd(s["xp"][:n], s["off"], s["w1"], s["w2"], expert)
+        b = O.grouped_ffn_bwd(s["dyp"][:n], s["xp"][:n], f["G"], f["U"], f["Hh"], s["off"],
+                              s["w1"], s["w2"], expert)
+        gu, dgu = host(t["gu"]), host(t["dgu"])
+        pairs = [("G", gu[:n, :H], f["G"]), ("h", host(t["h"])[:n], f["Hh"]),
+                 ("yp", host(t["yp"])[:n], f["Y"]), ("dG", dgu[:n, :H], b["dG"]),
+                 ("dxp", host(t["dxp"])[:n], b["dXp"])]
+        if expert == "swiglu":
+            pairs += [("U", gu[:n, H:], f["U"]), ("dU", dgu[:n, H:], b["dU"])]
+        for key, value, want in pairs:
+            errs[f"{key}{i}"] = assert_close(key, value, want, tol)
+        for key in ("gu", "h", "yp", "dgu", "dxp"):
+            assert torch.isnan(t[key][n:]).all(), f"{key}: a row past the groups was written"
+        for key, want in (("dw1", b["dW_gate_up"]), ("dw2", b["dW_down"])):
+            value = host(t[key])
+            for r, sz in enumerate(s["sizes"]):
+                w = want[r] + (s[key][r] if acc else 0.0)
+                if sz == 0:
+                    assert np.array_equal(value[r], w), f"{key} of empty group {r}"
+                else:
+                    errs[f"{key}.{i}.{r}"] = assert_close(f"{key}[{r}]", value[r], w, tol)
+    record_errors(f"gemm_tiles[{name}]", errs)
