@@ -300,6 +300,58 @@ int moe_combine_bwd(const void* dy, const void* yp, int dtype, int T, int d, int
                     hipStream_t stream);
 
 /*
+ * One layer's whole forward or backward in one call: the entry points above in
+ * order, for callers whose per-call cost counts (twelve calls of a tiny layer
+ * step took the host longer than the GPU).
+ *
+ *   moe_layer_fwd: moe_route_mask, moe_dispatch (rows to sets[0].xp),
+ *     moe_grouped_ffn_fwd_sets, moe_combine_fwd (adding sets[1].yp, the shared
+ *     experts' output, when n_sets == 2)
+ *   moe_layer_bwd: moe_combine_bwd (to sets[0].dyp), moe_grouped_ffn_bwd_sets,
+ *     moe_dispatch_bwd (into dx; added when n_sets == 2, whose sets[1].dxp is
+ *     dx), moe_route_bwd (added to dx)
+ *
+ * Every field has the meaning, layout and limits of the argument of that name;
+ * sets[0] are the routed experts (cap = T * min(k, E_r) rows, offsets written by
+ * the dispatch), sets[1] the shared ones.  ws_ffn is the workspace of the
+ * direction that is called.  A failed check returns its entry point's status,
+ * message and - in *where, unless where is NULL - name; the entry points before
+ * it have been launched.
+ */
+typedef struct moe_layer {
+  int dtype, T, d, E, k, E_r, gate, accumulate_dw, n_sets;
+  float inv_tau;
+  const void* x;
+  const void* w_router;
+  const float* router_bias;
+  const uint8_t* resident;
+  float* logits;
+  int32_t* topk_idx;
+  float* topk_w;
+  int32_t* topk_local;
+  int32_t* counts;
+  int32_t* offsets;
+  int32_t* perm;
+  int32_t* inv_perm;
+  void* ws_dispatch;
+  size_t ws_dispatch_bytes;
+  void* ws_ffn;
+  size_t ws_ffn_bytes;
+  void* y;             /* forward */
+  const void* dy;      /* from here on: backward */
+  float* d_topk_w;
+  float* dz;
+  float* dw_router;
+  float* d_bias;
+  void* dx;
+  void* ws_route;
+  size_t ws_route_bytes;
+  moe_ffn_set sets[2];
+} moe_layer;
+int moe_layer_fwd(const moe_layer* layer, const char** where, hipStream_t stream);
+int moe_layer_bwd(const moe_layer* layer, const char** where, hipStream_t stream);
+
+/*
  * Round boundary: expert-wise pseudo-gradient of the resident experts and its
  * average over the expert's replica group (Alg. 2, aggregation of the sparse
  * parameters within expert replica groups; Sec. 3.4 "Round structure").

@@ -25,7 +25,7 @@ EXPORTS = [
     "moe_grouped_ffn_fwd", "moe_grouped_ffn_bwd", "moe_grouped_ffn_fwd_workspace_size",
     "moe_grouped_ffn_fwd_sets",
     "moe_grouped_ffn_bwd_workspace_size", "moe_grouped_ffn_bwd_sets", "moe_combine_fwd",
-    "moe_combine_bwd",
+    "moe_combine_bwd", "moe_layer_fwd", "moe_layer_bwd",
     "moe_expert_delta", "moe_adamw_step", "moe_outer_nesterov", "moe_replica_mean",
     "moe_gen_placement", "moe_migration_map", "moe_copy_expert_rows", "moe_warmup_lr",
     "moe_adamw_step_rows", "moe_timing_enable", "moe_timing_collect",
@@ -65,6 +65,8 @@ _SIGS = {
     "moe_grouped_ffn_bwd_sets": (_I, [_P, _I, _I, _I, _I, _P, _Z, _P]),
     "moe_combine_fwd": (_I, [_P, _I, _I, _I, _I, _I, _P, _P, _P, _P, _P]),
     "moe_combine_bwd": (_I, [_P, _P, _I, _I, _I, _I, _I, _P, _P, _P, _P, _P]),
+    "moe_layer_fwd": (_I, [_P, C.POINTER(C.c_char_p), _P]),
+    "moe_layer_bwd": (_I, [_P, C.POINTER(C.c_char_p), _P]),
     "moe_expert_delta": (_I, [_P, _P, C.POINTER(C.c_void_p), _I, _Z, _P, _P, _P]),
     "moe_adamw_step": (_I, [_P, _P, _P, _P, _Z, _I, _F, _F, _F, _F, _F, _P, _P]),
     "moe_outer_nesterov": (_I, [_P, _P, _P, _P, _Z, _F, _F, _P, _P]),
@@ -90,6 +92,20 @@ class moe_ffn_set(C.Structure):
                 ("cap", _I), ("H", _I), ("n_groups", _I),
                 ("gu", _P), ("h", _P), ("yp", _P), ("dyp", _P), ("dgu", _P), ("dxp", _P),
                 ("dw_gate_up", _P), ("dw_down", _P), ("activation", _I)]
+
+
+class moe_layer(C.Structure):
+    """A whole layer step's arguments (struct moe_layer of include/moe_resident.h)."""
+    _fields_ = [(n, _I) for n in ("dtype", "T", "d", "E", "k", "E_r", "gate", "accumulate_dw",
+                                  "n_sets")]
+    _fields_ += [("inv_tau", _F)]
+    _fields_ += [(n, _P) for n in ("x", "w_router", "router_bias", "resident", "logits", "topk_idx",
+                                   "topk_w", "topk_local", "counts", "offsets", "perm", "inv_perm",
+                                   "ws_dispatch")]
+    _fields_ += [("ws_dispatch_bytes", _Z), ("ws_ffn", _P), ("ws_ffn_bytes", _Z)]
+    _fields_ += [(n, _P) for n in ("y", "dy", "d_topk_w", "dz", "dw_router", "d_bias", "dx",
+                                   "ws_route")]
+    _fields_ += [("ws_route_bytes", _Z), ("sets", moe_ffn_set * 2)]
 
 
 MOE_ACT_SWIGLU, MOE_ACT_SILU = 0, 1
@@ -255,6 +271,21 @@ def moe_combine_bwd(dy, yp, dtype, T, d, k, cap, topk_w, inv_perm, dyp, d_topk_w
     return _check("moe_combine_bwd", lib().moe_combine_bwd(
         _ptr(dy), _ptr(yp), dtype, T, d, k, cap, _ptr(topk_w), _ptr(inv_perm), _ptr(dyp),
         _ptr(d_topk_w), _stream(stream)))
+
+
+def _layer_call(fn, layer, stream):
+    where = C.c_char_p()
+    status = fn(C.byref(layer), C.byref(where), _stream(stream))
+    return _check(where.value.decode(), status) if status else status
+
+
+def moe_layer_fwd(layer, stream=None):
+    """layer: a moe_layer.  A failure names the entry point whose check failed."""
+    return _layer_call(lib().moe_layer_fwd, layer, stream)
+
+
+def moe_layer_bwd(layer, stream=None):
+    return _layer_call(lib().moe_layer_bwd, layer, stream)
 
 
 def moe_expert_delta(theta_start, theta_now, peers, n_peers, n_params, delta_local, delta_avg,

@@ -427,6 +427,48 @@ int moe_combine_bwd(const void* dy, const void* yp, int dtype, int T, int d, int
                     "moe_combine_bwd");
 }
 
+#define LAYER_CALL(fn, ...)            \
+  do {                                 \
+    const int r_ = fn(__VA_ARGS__);    \
+    if (r_ != MOE_OK) {                \
+      if (where) *where = #fn;         \
+      return r_;                       \
+    }                                  \
+  } while (0)
+
+int moe_layer_fwd(const moe_layer* l, const char** where, hipStream_t stream) {
+  if (where) *where = "moe_layer_fwd";
+  REQUIRE(l != nullptr, "layer must not be NULL");
+  const moe_ffn_set& f = l->sets[0];
+  LAYER_CALL(moe_route_mask, l->x, l->w_router, l->router_bias, l->dtype, l->T, l->d, l->E, l->k,
+             l->inv_tau, l->gate, l->resident, l->logits, l->topk_idx, l->topk_w, l->topk_local,
+             stream);
+  LAYER_CALL(moe_dispatch, l->x, l->dtype, l->T, l->d, l->k, l->E_r, l->topk_local, l->counts,
+             l->offsets, l->perm, l->inv_perm, const_cast<void*>(f.xp), l->ws_dispatch,
+             l->ws_dispatch_bytes, stream);
+  LAYER_CALL(moe_grouped_ffn_fwd_sets, l->sets, l->n_sets, l->dtype, l->d, l->ws_ffn,
+             l->ws_ffn_bytes, stream);
+  LAYER_CALL(moe_combine_fwd, f.yp, l->dtype, l->T, l->d, l->k, f.cap, l->topk_w, l->inv_perm,
+             l->n_sets == 2 ? l->sets[1].yp : nullptr, l->y, stream);
+  return ok();
+}
+
+int moe_layer_bwd(const moe_layer* l, const char** where, hipStream_t stream) {
+  if (where) *where = "moe_layer_bwd";
+  REQUIRE(l != nullptr, "layer must not be NULL");
+  const moe_ffn_set& f = l->sets[0];
+  LAYER_CALL(moe_combine_bwd, l->dy, f.yp, l->dtype, l->T, l->d, l->k, f.cap, l->topk_w,
+             l->inv_perm, const_cast<void*>(f.dyp), l->d_topk_w, stream);
+  LAYER_CALL(moe_grouped_ffn_bwd_sets, l->sets, l->n_sets, l->dtype, l->d, l->accumulate_dw,
+             l->ws_ffn, l->ws_ffn_bytes, stream);
+  LAYER_CALL(moe_dispatch_bwd, f.dxp, l->dtype, l->T, l->d, l->k, f.cap, l->inv_perm, l->dx,
+             l->n_sets == 2 ? 1 : 0, stream);
+  LAYER_CALL(moe_route_bwd, l->x, l->w_router, l->dtype, l->T, l->d, l->E, l->k, l->inv_tau,
+             l->gate, l->topk_idx, l->topk_w, l->logits, l->d_topk_w, l->dz, l->dw_router,
+             l->d_bias, l->dx, 1, l->ws_route, l->ws_route_bytes, stream);
+  return ok();
+}
+
 int moe_expert_delta(const float* theta_start, const float* theta_now,
                      const float* const* peers, int n_peers, size_t n_params, float* delta_local,
                      float* delta_avg, hipStream_t stream) {

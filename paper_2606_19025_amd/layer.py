@@ -1,7 +1,8 @@
 """One worker's local step through the resident-expert MoE layer.
 
 ``ResidentMoELayer`` owns the device buffers of one layer shape and issues the
-C entry points in order; it computes nothing itself.
+C entry points in order (through moe_layer_fwd / moe_layer_bwd, one call each);
+it computes nothing itself.
 
 Forward:  moe_route_mask -> moe_dispatch -> moe_grouped_ffn_fwd_sets (resident
           experts [+ shared experts on x, identity dispatch]) -> moe_combine_fwd
@@ -122,6 +123,9 @@ class ResidentMoELayer:
         """Raise ValueError unless t is a contiguous tensor on this layer's
         device with the given shape and dtype (the layer's own by default)."""
         dtype = self.dtype if dtype is None else dtype
+        if (isinstance(t, torch.Tensor) and t.dtype is dtype and t.shape == shape
+                and t.device == self.resident.device and t.is_contiguous()):
+            return
         if not isinstance(t, torch.Tensor):
             raise ValueError(f"{name} must be a tensor, got {type(t).__name__}")
         if t.device != self.resident.device:
@@ -145,16 +149,51 @@ class ResidentMoELayer:
         elif shared_gate_up is not None or shared_down is not None:
             raise ValueError("shared expert weights given to a layer built without them")
 
+    def _sets(self, x, w_gate_up, w_down, shared_gate_up, shared_down, dy=None):
+        """The expert sets of a step: the routed experts [, the shared ones]."""
+        sets = [B.ffn_set(self.xp, w_gate_up, w_down, self.offsets, self.cap, self.H, self.E_r,
+                          self.gu, self.h, yp=self.yp, dyp=self.dyp, dgu=self.dgu, dxp=self.dxp,
+                          dw_gate_up=self.dw_gate_up, dw_down=self.dw_down, activation=self.act)]
+        if self.Hs:
+            # the shared experts see every token with weight 1: their "dispatched
+            # rows" are x, their dyp is dy and their dxp is dx
+            sets.append(B.ffn_set(x, shared_gate_up, shared_down, self.s_offsets, self.T, self.Hs,
+                                  1, self.s_gu, self.s_h, yp=self.s_y, dyp=dy, dgu=self.s_dgu,
+                                  dxp=self.dx, dw_gate_up=self.s_dw_gate_up,
+                                  dw_down=self.s_dw_down, activation=self.act))
+        return sets
+
+    def _step(self, sets, ws, ws_bytes, x, w_router, router_bias=None, dy=None, accumulate_dw=0):
+        """The arguments of moe_layer_fwd / moe_layer_bwd, from this call's tensors and the
+        layer's buffers as they are now."""
+        p = torch.Tensor.data_ptr
+        return B.moe_layer(
+            self.dt, self.T, self.d, self.E, self.k, self.E_r, self.gate, accumulate_dw, len(sets),
+            self.inv_tau, p(x), p(w_router), None if router_bias is None else p(router_bias),
+            p(self.resident), p(self.logits), p(self.topk_idx), p(self.topk_w), p(self.topk_local),
+            p(self.counts), p(self.offsets), p(self.perm), p(self.inv_perm), p(self.ws_dispatch),
+            self.ws_dispatch_bytes, p(ws) if ws_bytes else None, ws_bytes, p(self.y),
+            None if dy is None else p(dy), p(self.dtopk_w), p(self.dz), p(self.dw_router),
+            p(self.d_bias), p(self.dx), p(self.ws_route), self.ws_route_bytes,
+            (B.moe_ffn_set * 2)(*sets))
+
     # ------------------------------------------------------------------ forward
     def forward(self, x, w_router, w_gate_up, w_down, router_bias=None, shared_gate_up=None,
                 shared_down=None, stream=None, hook=None):
         """hook: called before each library call (e.g. a cache flush between
         kernels for cold per-kernel timing); None in normal use."""
-        T, d, E, k, H, cap, dt = self.T, self.d, self.E, self.k, self.H, self.cap, self.dt
+        T, d, E, k, cap, dt = self.T, self.d, self.E, self.k, self.cap, self.dt
         self._check_weights(x, w_router, w_gate_up, w_down, shared_gate_up, shared_down)
         if router_bias is not None:
             self._check("router_bias", router_bias, (E,), torch.float32)
-        hook = hook or (lambda: None)
+        sets = self._sets(x, w_gate_up, w_down, shared_gate_up, shared_down)
+        if self.ws_fwd is None:
+            self.ws_fwd_bytes = B.moe_grouped_ffn_fwd_workspace_size(sets, dt, d)
+            self.ws_fwd = self._alloc(max(self.ws_fwd_bytes, 1), dt=torch.uint8)
+        if hook is None:
+            B.moe_layer_fwd(self._step(sets, self.ws_fwd, self.ws_fwd_bytes, x, w_router,
+                                       router_bias), stream)
+            return self.y
         hook()
         B.moe_route_mask(x, w_router, router_bias, dt, T, d, E, k, self.inv_tau, self.gate,
                          self.resident, self.logits, self.topk_idx, self.topk_w, self.topk_local,
@@ -163,47 +202,31 @@ class ResidentMoELayer:
         B.moe_dispatch(x, dt, T, d, k, self.E_r, self.topk_local, self.counts, self.offsets,
                        self.perm, self.inv_perm, self.xp, self.ws_dispatch, self.ws_dispatch_bytes,
                        stream)
-        sets = [B.ffn_set(self.xp, w_gate_up, w_down, self.offsets, cap, H, self.E_r, self.gu,
-                          self.h, yp=self.yp, activation=self.act)]
-        y_add = None
-        if self.Hs:
-            # the shared experts see every token: their "dispatched rows" are x
-            sets.append(B.ffn_set(x, shared_gate_up, shared_down, self.s_offsets, T, self.Hs, 1,
-                                  self.s_gu, self.s_h, yp=self.s_y, activation=self.act))
-            y_add = self.s_y
-        if self.ws_fwd is None:
-            self.ws_fwd_bytes = B.moe_grouped_ffn_fwd_workspace_size(sets, dt, d)
-            self.ws_fwd = self._alloc(max(self.ws_fwd_bytes, 1), dt=torch.uint8)
         hook()
         B.moe_grouped_ffn_fwd_sets(sets, dt, d, self.ws_fwd if self.ws_fwd_bytes else None,
                                    self.ws_fwd_bytes, stream)
         hook()
-        B.moe_combine_fwd(self.yp, dt, T, d, k, cap, self.topk_w, self.inv_perm, y_add, self.y,
-                          stream)
+        B.moe_combine_fwd(self.yp, dt, T, d, k, cap, self.topk_w, self.inv_perm,
+                          self.s_y if self.Hs else None, self.y, stream)
         return self.y
 
     # ----------------------------------------------------------------- backward
     def backward(self, dy, x, w_router, w_gate_up, w_down, shared_gate_up=None, shared_down=None,
                  accumulate_dw=0, stream=None, hook=None):
-        T, d, E, k, H, cap, dt = self.T, self.d, self.E, self.k, self.H, self.cap, self.dt
+        T, d, E, k, cap, dt = self.T, self.d, self.E, self.k, self.cap, self.dt
         self._check_weights(x, w_router, w_gate_up, w_down, shared_gate_up, shared_down)
         self._check("dy", dy, (T, d))
-        hook = hook or (lambda: None)
-        hook()
-        B.moe_combine_bwd(dy, self.yp, dt, T, d, k, cap, self.topk_w, self.inv_perm, self.dyp,
-                          self.dtopk_w, stream)
-        sets = [B.ffn_set(self.xp, w_gate_up, w_down, self.offsets, cap, H, self.E_r, self.gu,
-                          self.h, dyp=self.dyp, dgu=self.dgu, dxp=self.dxp,
-                          dw_gate_up=self.dw_gate_up, dw_down=self.dw_down, activation=self.act)]
-        if self.Hs:
-            # the shared experts see every token with weight 1: their dxp is dx
-            sets.append(B.ffn_set(x, shared_gate_up, shared_down, self.s_offsets, T, self.Hs, 1,
-                                  self.s_gu, self.s_h, dyp=dy, dgu=self.s_dgu, dxp=self.dx,
-                                  dw_gate_up=self.s_dw_gate_up, dw_down=self.s_dw_down,
-                                  activation=self.act))
+        sets = self._sets(x, w_gate_up, w_down, shared_gate_up, shared_down, dy)
         if self.ws_ffn is None:
             self.ws_ffn_bytes = B.moe_grouped_ffn_bwd_workspace_size(sets, dt, d)
             self.ws_ffn = self._alloc(self.ws_ffn_bytes, dt=torch.uint8)
+        if hook is None:
+            B.moe_layer_bwd(self._step(sets, self.ws_ffn, self.ws_ffn_bytes, x, w_router, dy=dy,
+                                       accumulate_dw=accumulate_dw), stream)
+            return self.dx
+        hook()
+        B.moe_combine_bwd(dy, self.yp, dt, T, d, k, cap, self.topk_w, self.inv_perm, self.dyp,
+                          self.dtopk_w, stream)
         hook()
         B.moe_grouped_ffn_bwd_sets(sets, dt, d, accumulate_dw, self.ws_ffn, self.ws_ffn_bytes,
                                    stream)
