@@ -133,6 +133,4 @@ enum TileSize { TILE_256x256, TILE_64x128, TILE_64x64, TILE_32x64 };
 hipError_t run_gemm_tile(int bf16, int ka, int kb, const GemmArgs* sets_a, int na,
                          const GemmArgs* sets_b, int nb, TileSize size, hipStream_t s);
 
-int num_cus();
-
 }  // namespace moe
