@@ -1289,8 +1289,12 @@ constexpr TileCost kTileCost[] = {{256, 256, 1.45, 6.0, 1.45, 6.0},
                                   {64, 128, 0.35, 1.6, 0.55, 6.0},
                                   {64, 64, 0.25, 1.1, 0.45, 5.0}};
 
-double launch_us(const TileCost& c, int ka, const GemmArgs* sa, int na, const GemmArgs* sb, int nb,
-                 bool parts) {
+struct Estimate {
+  double us;
+  bool parts;  // the long tiles outlast the others' work: cut them into K parts
+};
+Estimate estimate(const TileCost& c, int ka, const GemmArgs* sa, int na, const GemmArgs* sb, int nb,
+                  bool parts) {
   double sum = 0, longest = 0, most_parts = 0;
   for (int q = 0; q < na + nb; ++q) {
     const GemmArgs& a = q < na ? sa[q] : sb[q - na];
@@ -1309,11 +1313,19 @@ double launch_us(const TileCost& c, int ka, const GemmArgs* sa, int na, const Ge
   }
   sum /= num_cus();
   const double t = std::max(longest, sum + 0.3 * longest);
-  if (most_parts <= sum * 4 / 3) return std::max(t, most_parts);
-  return std::max(t, sum * 4 / 3) + 20;  // partial rows, their sum and its launch
+  // (in a merged launch the long tiles run beside many short ones, slower than
+  // alone; 20: the partial rows, their sum and its launch).  Mid-size dX + dW_gu
+  // 156 + 9 us with parts, 183 without; fine-grained down projection, sigma-MoE dX
+  // and the like level, and a launch less without.
+  const double uncut = std::max(t, (nb ? 1.35 : 1.0) * most_parts), cut = std::max(t, sum * 4 / 3) + 20;
+  return {std::min(uncut, cut), cut < uncut};
 }
 
-TileSize choose_tiles(int ka, const GemmArgs* sa, int na, const GemmArgs* sb, int nb, bool parts) {
+// parts: in, whether the launch may cut long tiles into K parts; out, whether it
+// should (a launch that may has its partial rows' sum launched after it).
+TileSize choose_tiles(int ka, const GemmArgs* sa, int na, const GemmArgs* sb, int nb, bool* parts) {
+  const bool may = *parts;
+  *parts = false;
   // about 32 rows per group or fewer: the weights' stream is all, with the
   // deepest ring (48 tokens over the fine-grained experts: GU 51, down projection
   // 29 us against 53 and 32 with 64 x 64 tiles, 57 and 49 + 5 with 256 x 256;
@@ -1325,10 +1337,13 @@ TileSize choose_tiles(int ka, const GemmArgs* sa, int na, const GemmArgs* sb, in
       few = few && (sa[q].n_groups == 1 ? sa[q].cap <= 64 : 0.6 * sa[q].cap <= 32.0 * sa[q].n_groups);
     if (few) return TILE_32x64;
   }
-  const double big = launch_us(kTileCost[0], ka, sa, na, sb, nb, parts);
-  const double mid = launch_us(kTileCost[1], ka, sa, na, sb, nb, false);
-  const double small = launch_us(kTileCost[2], ka, sa, na, sb, nb, false);
-  if (big <= mid && big <= small) return TILE_256x256;
+  const Estimate big = estimate(kTileCost[0], ka, sa, na, sb, nb, may);
+  const double mid = estimate(kTileCost[1], ka, sa, na, sb, nb, false).us;
+  const double small = estimate(kTileCost[2], ka, sa, na, sb, nb, false).us;
+  if (big.us <= mid && big.us <= small) {
+    *parts = big.parts;
+    return TILE_256x256;
+  }
   return mid <= small ? TILE_64x128 : TILE_64x64;
 }
 
@@ -1378,7 +1393,8 @@ hipError_t launch_ffn_fwd_sets(const moe_ffn_set* sets, int n_sets, int bf16, in
     b.N = d; b.K = f.H;
   }
   const int first = silu ? UP_FWD : GU_FWD;
-  TileSize size = bf16 ? choose_tiles(first, g, n_sets, nullptr, 0, false) : TILE_64x128;
+  bool parts = false;
+  TileSize size = bf16 ? choose_tiles(first, g, n_sets, nullptr, 0, &parts) : TILE_64x128;
   hipError_t e;
   if (bf16 && size == TILE_256x256)
     e = silu ? run_gemm_bf16<UP_FWD, UP_FWD>(g, n_sets, nullptr, 0, s, nullptr)
@@ -1386,10 +1402,11 @@ hipError_t launch_ffn_fwd_sets(const moe_ffn_set* sets, int n_sets, int bf16, in
   else
     e = run_gemm_tile(bf16, first, first, g, n_sets, nullptr, 0, size, s);
   if (e != hipSuccess) return e;
-  if (bf16) size = choose_tiles(DOWN_FWD, o, n_sets, nullptr, 0, ws != nullptr);
+  parts = ws != nullptr;
+  if (bf16) size = choose_tiles(DOWN_FWD, o, n_sets, nullptr, 0, &parts);
   if (!bf16 || size != TILE_256x256)
     return run_gemm_tile(bf16, DOWN_FWD, DOWN_FWD, o, n_sets, nullptr, 0, size, s);
-  assign_row_parts(o, sets, n_sets, bf16, d, static_cast<char*>(ws));
+  if (parts) assign_row_parts(o, sets, n_sets, bf16, d, static_cast<char*>(ws));
   e = run_gemm_bf16<DOWN_FWD, DOWN_FWD>(o, n_sets, nullptr, 0, s, nullptr);
   return e != hipSuccess ? e : reduce_row_parts(o, n_sets, s);
 }
@@ -1439,9 +1456,11 @@ hipError_t launch_ffn_bwd_sets(const moe_ffn_set* sets, int n_sets, int bf16, in
   // two launches of two independent kinds each: dHh with dW_d (both read dY),
   // then dX with dW_gu (both read dG/dU)
   TileSize size1 = TILE_64x128, size2 = TILE_64x128;
+  bool parts = ws != nullptr;
   if (bf16) {
-    size1 = choose_tiles(silu ? DH_BWD : DHH_BWD, hh, n_sets, wd, n_sets, false);
-    size2 = choose_tiles(DX_BWD, dx, n_sets, wgu, n_sets, ws != nullptr);
+    bool none = false;
+    size1 = choose_tiles(silu ? DH_BWD : DHH_BWD, hh, n_sets, wd, n_sets, &none);
+    size2 = choose_tiles(DX_BWD, dx, n_sets, wgu, n_sets, &parts);
   }
   const bool large1 = bf16 && size1 == TILE_256x256, large2 = bf16 && size2 == TILE_256x256;
   // a single large group's dW split by rows, in the large tiles
@@ -1474,7 +1493,7 @@ hipError_t launch_ffn_bwd_sets(const moe_ffn_set* sets, int n_sets, int bf16, in
     e = run_gemm_tile(bf16, silu ? DH_BWD : DHH_BWD, DWD, hh, n_sets, wd, n_sets, size1, s);
   if (e != hipSuccess) return e;
   if (large2) {
-    if (ws) assign_row_parts(dx, sets, n_sets, bf16, d, rows_ws);
+    if (parts) assign_row_parts(dx, sets, n_sets, bf16, d, rows_ws);
     e = run_gemm_bf16<DX_BWD, DWGU>(dx, n_sets, wgu, n_sets, s, ws ? counters + N_XCD : nullptr);
     if (e != hipSuccess) return e;
     e = reduce_row_parts(dx, n_sets, s);

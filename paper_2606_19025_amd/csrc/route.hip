@@ -615,13 +615,23 @@ __global__ __launch_bounds__(256) void route_dz_kernel(RouteBwdArgs a) {
   float s = 0.f;
   for (int j = lane; j < a.k; j += 64) s += a.tw[o + j] * a.dtw[o + j];
   s = wave_sum(s);
-  float zmax = 0.f, denom = 1.f;
+  // softmax over all E (at most 256): the row's logits are read once
+  float z[4], zmax = 0.f, denom = 1.f;
   if (a.gate == 1) {
     float m = -INFINITY;
-    for (int e = lane; e < a.E; e += 64) m = fmaxf(m, a.logits[(size_t)t * a.E + e]);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int e = q * 64 + lane;
+      z[q] = e < a.E ? a.logits[(size_t)t * a.E + e] : -INFINITY;
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (q * 64 + lane < a.E) m = fmaxf(m, z[q]);
     zmax = wave_max(m);
     float acc = 0.f;
-    for (int e = lane; e < a.E; e += 64) acc += expf(a.logits[(size_t)t * a.E + e] - zmax);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (q * 64 + lane < a.E) acc += z[q] = expf(z[q] - zmax);
     denom = wave_sum(acc);
   }
   // lane j holds route j's expert and the route's own share of the gradient
@@ -633,7 +643,10 @@ __global__ __launch_bounds__(256) void route_dz_kernel(RouteBwdArgs a) {
   };
   const int my_e = held && lane < a.k ? a.idx[o + lane] : -1;
   const float my_g = held && lane < a.k ? share(lane) : 0.f;
-  for (int e = lane; e - lane < a.E; e += 64) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int e = q * 64 + lane;
+    if (q * 64 >= a.E) break;
     float g = 0.f;
     if (held) {
       for (int j = a.k - 1; j >= 0; --j) {
@@ -646,7 +659,7 @@ __global__ __launch_bounds__(256) void route_dz_kernel(RouteBwdArgs a) {
         if (a.idx[o + j] == e) g = share(j);
     }
     if (e < a.E) {
-      if (a.gate == 1) g = expf(a.logits[(size_t)t * a.E + e] - zmax) / denom * (g - s);
+      if (a.gate == 1) g = z[q] / denom * (g - s);
       a.dz[(size_t)t * a.E + e] = g;
     }
   }
