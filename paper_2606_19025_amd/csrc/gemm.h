@@ -50,6 +50,7 @@ DEVI int clamp_row(int v, int cap) { return v < 0 ? 0 : (v > cap ? cap : v); }
 constexpr int kMaxGroups = 256;
 struct GroupTable {
   int c[kMaxGroups + 1], b[kMaxGroups + 1], p[kMaxGroups + 1];
+  int uneven;  // (ragged in K) a group's tiles take over 1.25 times the average
 };
 
 DEVI int wave_incl_max(int v) {
@@ -72,8 +73,11 @@ DEVI int wave_incl_sum(int v) {
 }
 
 // Fill t from set a for m-tiles of BM rows (one wave; n_groups <= kMaxGroups).
+// tile_rows: what a tile of a set ragged in K takes besides its group's rows (fill
+// and epilogue, in rows).  (Found here, where the rows are at hand: a pass of
+// its own over the table cost every launch 1 to 1.5 us.)
 template <int BM>
-DEVI void build_group_table(const GemmArgs& a, GroupTable& t) {
+DEVI void build_group_table(const GemmArgs& a, GroupTable& t, int tile_rows) {
   const int lane = threadIdx.x & 63;
   const int ng = a.n_groups;
   int run = 0;
@@ -90,13 +94,18 @@ DEVI void build_group_table(const GemmArgs& a, GroupTable& t) {
   }
   WAIT_LGKMCNT(0);  // the wave's own table writes (lanes read their neighbours')
   int acc = 0;
+  bool uneven = false;
+  const float most = 1.25f * ((float)run + (float)tile_rows * (float)ng);
   for (int g0 = 0; g0 <= ng; g0 += 64) {
     const int g = g0 + lane;
-    const int tiles = g < ng ? (t.b[g + 1] - t.b[g] + BM - 1) / BM : 0;
+    const int rows = g < ng ? t.b[g + 1] - t.b[g] : 0;
+    const int tiles = (rows + BM - 1) / BM;
+    uneven = uneven || __ballot((float)(rows + tile_rows) * (float)ng > most) != 0;
     const int inc = wave_incl_sum(tiles);
     if (g <= ng) t.p[g] = acc + inc - tiles;
     acc += __shfl(inc, 63, 64);
   }
+  if (lane == 0) t.uneven = uneven;
 }
 
 // Kernel argument of the GEMM kernels: up to kMaxSets sets of groups, each of

@@ -413,6 +413,31 @@ DEVI void tile_decode(const GemmArgs& a, const GroupTable& gt, int t, int m_tile
   }
 }
 
+// First tile of XCD x's share (x = N_XCD: the number of tiles) of the tot tiles of a
+// set ragged in K: an eighth of their time.  For uneven groups: by the number of
+// tiles, the XCDs that got a large group worked on alone.  Zipf-sized
+// groups, backward alone: 16384 rows in 16, d = 2048, H = 1408 1051 -> 740 us (equal
+// groups 668), 32768 in 40 2130 -> 1567, 6000 in 10, d = 1536 343 -> 288.  Even
+// groups keep an eighth of the tiles: its shares end at the groups' own ends (by time
+// the equal groups took 695).
+constexpr int kTileRows = 256;  // a tile's epilogue and fill, in rows of its reduction
+DEVI int time_share(const GemmArgs& a, const GroupTable& t, int tot, int x) {
+  const int lane = threadIdx.x & 63, ng = a.n_groups;
+  const long per_group = tot / ng;
+  // time of a tile of each group before group g
+  auto before = [&](int g) { return (long)(t.b[g] - t.b[0]) + (long)kTileRows * g; };
+  const long target = before(ng) * per_group * x / N_XCD;
+  int g = 0;
+  for (int g0 = 0; g0 < ng; g0 += 64) {
+    const int gg = g0 + lane;
+    g += __builtin_popcountll(__ballot(gg < ng && before(gg + 1) * per_group <= target));
+  }
+  g = __builtin_amdgcn_readfirstlane(g);
+  int first = g * (int)per_group;
+  if (g < ng) first += (int)((target - before(g) * per_group) / (before(g + 1) - before(g)));
+  return __builtin_amdgcn_readfirstlane(first);
+}
+
 template <int KIND>
 DEVI int col_tiles(const GemmArgs& a) {
   return ((KIND == GU_FWD ? 2 * a.H : a.N) + GT - 1) / GT;
@@ -457,14 +482,14 @@ __global__ __launch_bounds__(512, 2) void gemm_bf16_kernel(GemmLaunch L) {
   };
 
   // XCD-aware assignment (the grid is a multiple of N_XCD blocks): XCD x takes
-  // the x-th eighth of every set's tile range (so each XCD gets an equal share
-  // of each set's work), in set order.  Its blocks deal these tiles
+  // the x-th eighth of every set's tile range, by number or (time_share) by time
+  // (so each XCD gets an equal share of each set's work), in set order.  Its blocks deal these tiles
   // round-robin, or - with counters - each block takes the XCD's next tile
   // when it finishes one (tiles of unequal K then balance across blocks).
   const int per_xcd = gridDim.x / N_XCD;
   const int xcd = blockIdx.x % N_XCD;
   __shared__ GroupTable gtab[kMaxSets];
-  if (wave < L.n_sets) build_group_table<GT>(L.s[wave], gtab[wave]);
+  if (wave < L.n_sets) build_group_table<GT>(L.s[wave], gtab[wave], kTileRows);
   __syncthreads();
   // per set: m-tiles, n-tiles, this XCD's first tile and its reduction
   // length per tile (rows per group for the K-ragged kinds, from the table)
@@ -518,6 +543,13 @@ __global__ __launch_bounds__(512, 2) void gemm_bf16_kernel(GemmLaunch L) {
     const int tot = q < L.n_sets ? mt[q] * prt[q] * ntl[q] : 0;
     lo[q] = (int)((long)tot * xcd / N_XCD);
     cnt[q] = (int)((long)tot * (xcd + 1) / N_XCD) - lo[q];
+    if constexpr (KA != KB) {  // every second kind is ragged in K
+      if (q < L.n_sets && L.kind_b[q] != 0 && L.s[q].n_groups > 1 &&
+          __builtin_amdgcn_readfirstlane(gtab[q].uneven)) {
+        lo[q] = time_share(L.s[q], gtab[q], tot, xcd);
+        cnt[q] = time_share(L.s[q], gtab[q], tot, xcd + 1) - lo[q];
+      }
+    }
   }
   // dealing order of the sets: with dynamic dealing the longest reduction per
   // tile first (so that long tiles do not start last and short ones fill the

@@ -508,18 +508,20 @@ template <int KIND>
 DEVI constexpr int cols_of(const GemmArgs& a) { return KIND == GU_FWD ? 2 * a.H : a.N; }
 
 // Weight gradients (ragged in K): a group's tiles all take its own number of
-// k-steps, so every XCD takes an eighth of each group's per_group tiles, XCD x
-// the ((x + g) % 8)-th of group g (uneven eighths then even out).  With an
-// eighth of all tiles, the XCDs that got a large group worked on alone.  Zipf-sized
-// groups, fp32: 1531 rows in 6, d = 520, H = 1408, forward and backward 327 -> 264
-// us; 4096 rows in 8, d = 1024, the same H, backward 1190 -> 619 (groups of equal
-// size 601 -> 598); bf16, 3000 rows in 24, d = 960, H = 512 73 -> 64.
+// k-steps, so of uneven groups every XCD takes an eighth of each one's per_group
+// tiles, XCD x the ((x + g) % 8)-th of group g (eighths that differ by a tile then
+// even out).  With an eighth of all tiles, the XCDs that got a large group worked
+// on alone.  Zipf-sized groups, fp32: 1531 rows in 6, d = 520, H = 1408, forward
+// and backward 327 -> 264 us; 4096 rows in 8, d = 1024, the same H, backward 1190 ->
+// 619; bf16, 3000 rows in 24, d = 960, H = 512 73 -> 64.  Even groups keep an eighth
+// of all (fewer XCDs read the same rows: 1500 rows in 12, d = 768, H = 704: 51 -> 49 us).
+constexpr int kTileRows = 128;  // a tile's fill and epilogue, in rows of its reduction
 DEVI int eighth(int per_group, int x) { return (int)((long)per_group * x / kXcds); }
 
-// Tile order: XCD x takes the x-th eighth of every M-ragged set's tiles (blocks go
-// to the XCDs round-robin by id), in bands of kBand m-tiles, and of every group's
-// tiles of the other sets.  The grid covers the largest number of tiles that the
-// group sizes can give; blocks past the last tile end at once.
+// Tile order: XCD x takes the x-th eighth of every set's tiles (blocks go to the XCDs
+// round-robin by id), in bands of kBand m-tiles, or an eighth of every uneven group's.
+// The grid covers the largest number of tiles that the group sizes can give; blocks
+// past the last tile end at once.
 template <class T, int KA, int KB, int MI, int NJ, int NS>
 __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(GemmLaunch L) {
   constexpr int BM = 32 * MI, BN = 32 * NJ;
@@ -529,7 +531,7 @@ __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(GemmLaunch L) {
   GroupTable* gtab = reinterpret_cast<GroupTable*>(lds);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
-  if (wave < L.n_sets) build_group_table<BM>(L.s[wave], gtab[wave]);
+  if (wave < L.n_sets) build_group_table<BM>(L.s[wave], gtab[wave], kTileRows);
   __syncthreads();
   const int xcd = blockIdx.x % kXcds;
   int i = blockIdx.x / kXcds;  // this block's tile among the XCD's
@@ -540,9 +542,10 @@ __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(GemmLaunch L) {
     const bool kb = KA != KB && L.kind_b[q] != 0;
     const bool mrag = kb ? Kind<KB>::MRAG : Kind<KA>::MRAG;
     const int cols = kb ? cols_of<KB>(a) : cols_of<KA>(a);
+    const int mt_g = mrag ? 0 : (a.M + BM - 1) / BM;
     const int n_tiles = (cols + BN - 1) / BN;
-    if (!mrag) {
-      const int mt_g = (a.M + BM - 1) / BM, per_group = mt_g * n_tiles;
+    if (!mrag && __builtin_amdgcn_readfirstlane(gtab[q].uneven)) {
+      const int per_group = mt_g * n_tiles;
       auto share = [&](int g) {
         const int y = (xcd + g) % kXcds;
         return eighth(per_group, y + 1) - eighth(per_group, y);
@@ -569,7 +572,7 @@ __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(GemmLaunch L) {
       tl.rows = max(0, gtab[q].c[g + 1] - tl.row0);
       break;
     }
-    const int m_tiles = __builtin_amdgcn_readfirstlane(gtab[q].p[a.n_groups]);
+    const int m_tiles = __builtin_amdgcn_readfirstlane(mrag ? gtab[q].p[a.n_groups] : a.n_groups * mt_g);
     const long tot = (long)m_tiles * n_tiles;
     const long lo = tot * xcd / kXcds;
     const int cnt = (int)(tot * (xcd + 1) / kXcds - lo);
@@ -585,16 +588,23 @@ __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(GemmLaunch L) {
     const int r = (int)(t - band * kBand * n_tiles);
     const int mt = first_m + r % band_m;
     tl.tile_n = r / band_m;
-    int g = 0;  // the groups whose m-tiles all lie before this one
-    for (int g0 = 0; g0 < a.n_groups; g0 += 64) {
-      const int gg = g0 + lane;
-      g += __builtin_popcountll(__ballot(gg < a.n_groups && gtab[q].p[gg + 1] <= mt));
+    if (mrag) {
+      int g = 0;  // the groups whose m-tiles all lie before this one
+      for (int g0 = 0; g0 < a.n_groups; g0 += 64) {
+        const int gg = g0 + lane;
+        g += __builtin_popcountll(__ballot(gg < a.n_groups && gtab[q].p[gg + 1] <= mt));
+      }
+      g = __builtin_amdgcn_readfirstlane(g);
+      tl.g = g;
+      tl.row0 = gtab[q].b[g] + (mt - gtab[q].p[g]) * BM;
+      tl.rows = min(BM, gtab[q].b[g + 1] - tl.row0);
+      tl.m0 = 0;
+    } else {
+      tl.g = mt / mt_g;
+      tl.m0 = mt % mt_g * BM;
+      tl.row0 = gtab[q].c[tl.g];
+      tl.rows = max(0, gtab[q].c[tl.g + 1] - tl.row0);
     }
-    g = __builtin_amdgcn_readfirstlane(g);
-    tl.g = g;
-    tl.row0 = gtab[q].b[g] + (mt - gtab[q].p[g]) * BM;
-    tl.rows = min(BM, gtab[q].b[g + 1] - tl.row0);
-    tl.m0 = 0;
     break;
   }
   tl.row0 = __builtin_amdgcn_readfirstlane(tl.row0);
