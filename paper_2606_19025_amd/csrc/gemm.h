@@ -75,7 +75,7 @@ DEVI int wave_incl_sum(int v) {
 // Fill t from set a for m-tiles of BM rows (one wave; n_groups <= kMaxGroups).
 // tile_rows: what a tile of a set ragged in K takes besides its group's rows (fill
 // and epilogue, in rows).  (Found here, where the rows are at hand: a pass of
-// its own over the table cost every launch 1 to 1.5 us.)
+// its own over the table was slower.)
 template <int BM>
 DEVI void build_group_table(const GemmArgs& a, GroupTable& t, int tile_rows) {
   const int lane = threadIdx.x & 63;
@@ -105,7 +105,8 @@ DEVI void build_group_table(const GemmArgs& a, GroupTable& t, int tile_rows) {
     if (g <= ng) t.p[g] = acc + inc - tiles;
     acc += __shfl(inc, 63, 64);
   }
-  if (lane == 0) t.uneven = uneven;
+  t.uneven = uneven;  // (the same from every lane)
+  WAIT_LGKMCNT(0);
 }
 
 // Kernel argument of the GEMM kernels: up to kMaxSets sets of groups, each of

@@ -483,13 +483,30 @@ __global__ __launch_bounds__(512, 2) void gemm_bf16_kernel(GemmLaunch L) {
 
   // XCD-aware assignment (the grid is a multiple of N_XCD blocks): XCD x takes
   // the x-th eighth of every set's tile range, by number or (time_share) by time
-  // (so each XCD gets an equal share of each set's work), in set order.  Its blocks deal these tiles
-  // round-robin, or - with counters - each block takes the XCD's next tile
-  // when it finishes one (tiles of unequal K then balance across blocks).
+  // (so each XCD gets an equal share of each set's work), in set order.  Its
+  // blocks deal these tiles round-robin, or - with counters - each block takes
+  // the XCD's next tile when it finishes one (tiles of unequal K then balance
+  // across blocks).
   const int per_xcd = gridDim.x / N_XCD;
   const int xcd = blockIdx.x % N_XCD;
   __shared__ GroupTable gtab[kMaxSets];
-  if (wave < L.n_sets) build_group_table<GT>(L.s[wave], gtab[wave], kTileRows);
+  __shared__ int shares[kMaxSets][2];  // of uneven sets: this XCD's first tile and the next's
+  if (wave < L.n_sets) {
+    const GemmArgs& a = L.s[wave];
+    build_group_table<GT>(a, gtab[wave], kTileRows);
+    if constexpr (KA != KB) {  // every second kind is ragged in K
+      // (here, once and by one wave: in line with each set's other numbers below it
+      // cost even launches 1 to 1.5 us each; mid-size step 448 -> 452)
+      if (L.kind_b[wave] != 0 && gtab[wave].uneven) {
+        const int tot = m_tile_count<KB>(a, gtab[wave]) * col_tiles<KB>(a);
+#pragma unroll 1
+        for (int u = 0; u < 2; ++u) {
+          const int at = time_share(a, gtab[wave], tot, xcd + u);
+          if (lane == 0) shares[wave][u] = at;
+        }
+      }
+    }
+  }
   __syncthreads();
   // per set: m-tiles, n-tiles, this XCD's first tile and its reduction
   // length per tile (rows per group for the K-ragged kinds, from the table)
@@ -543,11 +560,10 @@ __global__ __launch_bounds__(512, 2) void gemm_bf16_kernel(GemmLaunch L) {
     const int tot = q < L.n_sets ? mt[q] * prt[q] * ntl[q] : 0;
     lo[q] = (int)((long)tot * xcd / N_XCD);
     cnt[q] = (int)((long)tot * (xcd + 1) / N_XCD) - lo[q];
-    if constexpr (KA != KB) {  // every second kind is ragged in K
-      if (q < L.n_sets && L.kind_b[q] != 0 && L.s[q].n_groups > 1 &&
-          __builtin_amdgcn_readfirstlane(gtab[q].uneven)) {
-        lo[q] = time_share(L.s[q], gtab[q], tot, xcd);
-        cnt[q] = time_share(L.s[q], gtab[q], tot, xcd + 1) - lo[q];
+    if constexpr (KA != KB) {
+      if (q < L.n_sets && L.kind_b[q] != 0 && __builtin_amdgcn_readfirstlane(gtab[q].uneven)) {
+        lo[q] = __builtin_amdgcn_readfirstlane(shares[q][0]);
+        cnt[q] = __builtin_amdgcn_readfirstlane(shares[q][1]) - lo[q];
       }
     }
   }

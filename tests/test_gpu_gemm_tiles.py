@@ -33,6 +33,9 @@ CASES = {
     "rows-64": ([[63, 64, 65, 0, 127, 129, 1, 200]], 320, [704], "swiglu", True, 0, "0000"),
     "rows-64-silu": ([[500, 3, 65, 0, 129]], 1088, [192], "silu", True, 1, "0000"),
     "rows-64-shared": ([[260, 90, 0, 511], [861]], 448, [576, 1152], "swiglu", True, 0, "0000"),
+    # more than eight uneven groups, whose weight-gradient tiles each XCD shares
+    "many-uneven-groups": ([[5 * (i % 17) if i % 9 else 300 for i in range(70)]], 192, [192],
+                           "swiglu", True, 1, "0000"),
     "many-groups": ([[5 * (i % 17) for i in range(70)]], 64, [64], "swiglu", True, 0, "0000"),
 }
 
