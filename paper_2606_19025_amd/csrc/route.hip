@@ -7,8 +7,8 @@
 //   (tokens x experts tiles, the d reduction split over the 8 waves and summed
 //   in a fixed order through LDS; x and, for up to 64 experts, W_r rows are
 //   read whole and staged in LDS); for more experts the waves split the
-//   experts, and fp32 layers do the same on v_mfma_f32_32x32x2_f32
-//   (logits_ring).  For
+//   experts (logits_ring).  fp32 layers run one v_mfma_f32_16x16x4_f32 chain
+//   per logit (logits_f32).  For
 //   k <= 8 every wave then selects for 4 tokens, 16 lanes per token
 //   (select_groups, row maxima by DPP); for larger k each wave takes tokens
 //   one at a time, lane = expert, with k wave-wide (max logit, min id)
@@ -294,34 +294,32 @@ DEVI void route_dma(const void* p, char* base) {
                  : "m0", "memory");
 }
 
-// Logits of fp32 layers, and of bf16 ones with more than 64 experts.  The waves
+// bf16 logits of more than 64 experts.  The waves
 // form EG expert groups (32 experts each) x KG = 8 / EG groups of d slices: a
 // wave's 32 x 32 tile of (token, expert) runs over the slices kg, kg + KG, ...
 // of 128 bytes, so W_r is read once per block, each row by one wave, and only
 // KG partial sums are left to add.  (One wave for all experts of a d slice held
 // 128 accumulators at 256 experts and added them to LDS wave after wave:
-// 5003 tokens, d = 1536, 256 experts took 82 us.  fp32 dot products by one
-// thread each read every operand element with a load of its own.)
+// 5003 tokens, d = 1536, 256 experts took 82 us.)
 // x and W_r rows go to LDS by DMA as whole 128-byte pieces through a ring of NS
 // stages.  Chunk c (16 bytes) of row r sits at chunk c ^ ((r >> 1) & 7).
-// bf16: v_mfma_f32_32x32x16_bf16; fp32: v_mfma_f32_32x32x2_f32.  Four
-// accumulators in turn keep the chains of additions short.  VEC: rows are
-// 16-byte aligned; otherwise the DMA moves 4 bytes per lane.  The 256-expert
-// case above now takes 31 us, bound by each CU's read of W_r (786 KB) from L2.
-template <class T, int EG, bool VEC>
+// Four accumulators in turn keep the chains of additions short.
+// The 256-expert case above now takes 31 us, bound by each CU's read of W_r
+// (786 KB) from L2.
+template <int EG>
 DEVI void logits_ring(const RouteFwdArgs& a, int t0, float* zl, int ldz) {
   constexpr int KG = RT_WAVES / EG;
   constexpr int EP = EG * 32;
-  constexpr int KW = 128 / sizeof(T);             // elements of a slice
+  constexpr int KW = 64;                          // elements of a slice
   constexpr int W_BYTES = RT_WAVES * 4096;        // each wave's 32 W_r rows
   constexpr int STAGE = W_BYTES + KG * 4096;      // and the KG slices' 32 x rows
-  constexpr int NS = EG == 1 ? 2 : 3;
+  constexpr int NS = 3;
   constexpr int XP = KG >= 2 ? KG / 2 : 1;        // KiB of x per wave and stage
-  constexpr int PER = (4 + XP) * (VEC ? 1 : 4);   // DMA loads per wave and stage
+  constexpr int PER = 4 + XP;                     // DMA loads per wave and stage
   static_assert(NS * STAGE >= KG * RT_TOK * EP * 4, "the partial sums reuse the ring");
   __shared__ __attribute__((aligned(1024))) char ring[NS * STAGE];
-  const T* x = static_cast<const T*>(a.x);
-  const T* w = static_cast<const T*>(a.w);
+  const bf16_t* x = static_cast<const bf16_t*>(a.x);
+  const bf16_t* w = static_cast<const bf16_t*>(a.w);
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int eg = wave % EG, kg = wave / EG;
@@ -329,21 +327,10 @@ DEVI void logits_ring(const RouteFwdArgs& a, int t0, float* zl, int ldz) {
   const int n_stages = (n_slices + KG - 1) / KG;
   // one KiB (8 rows of 128 bytes, from row r0) of slice sl of p into dst; row
   // index clamped to the last (the results of the rows past it are not used)
-  auto kib = [&](const T* p, int r0, int last, int sl, char* dst) {
-    if constexpr (VEC) {
-      const int r = r0 + (lane >> 3);
-      const int c = ((lane & 7) ^ ((r >> 1) & 7)) * (16 / (int)sizeof(T)) + sl * KW;
-      route_dma<true>(c < a.d ? (const void*)(p + (size_t)min(r, last) * a.d + c) : kRouteZeros, dst);
-    } else {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int r = r0 + 2 * q + (lane >> 5);
-        const int ch = ((lane >> 2) & 7) ^ ((r >> 1) & 7);
-        const int c = ch * 4 + (lane & 3) + sl * KW;
-        route_dma<false>(c < a.d ? (const void*)(p + (size_t)min(r, last) * a.d + c) : kRouteZeros,
-                         dst + q * 256);
-      }
-    }
+  auto kib = [&](const bf16_t* p, int r0, int last, int sl, char* dst) {
+    const int r = r0 + (lane >> 3);
+    const int c = ((lane & 7) ^ ((r >> 1) & 7)) * 8 + sl * KW;
+    route_dma<true>(c < a.d ? (const void*)(p + (size_t)min(r, last) * a.d + c) : kRouteZeros, dst);
   };
   auto load = [&](int stage) {
     char* st = ring + stage % NS * STAGE;
@@ -371,17 +358,9 @@ DEVI void logits_ring(const RouteFwdArgs& a, int t0, float* zl, int ldz) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int o = row * 128 + (((2 * q + half) ^ ((row >> 1) & 7)) << 4);
-      if constexpr (sizeof(T) == 2) {
-        acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8_t*>(xl + o),
-                                                         *reinterpret_cast<const bf16x8_t*>(wl + o),
-                                                         acc[q], 0, 0, 0);
-      } else {
-        const f32x4_t xv = *reinterpret_cast<const f32x4_t*>(xl + o);
-        const f32x4_t wv = *reinterpret_cast<const f32x4_t*>(wl + o);
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          acc[e] = __builtin_amdgcn_mfma_f32_32x32x2f32(xv[e], wv[e], acc[e], 0, 0, 0);
-      }
+      acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8_t*>(xl + o),
+                                                       *reinterpret_cast<const bf16x8_t*>(wl + o),
+                                                       acc[q], 0, 0, 0);
     }
   }
   __syncthreads();  // the partial sums take the ring's place
@@ -393,6 +372,128 @@ DEVI void logits_ring(const RouteFwdArgs& a, int t0, float* zl, int ldz) {
   }
   __syncthreads();
   finish_logits<EP, KG>(a, t0, part, zl, ldz);
+}
+
+// fp32 logits.  A logit is one chain of fused multiply-adds in the order of d,
+// the order that a plain loop takes: v_mfma_f32_16x16x4_f32 adds its four products
+// one after another, each rounded once, so a chain of them gives the loop's bits.
+// (Ranks hang on these bits: with d split over waves and four accumulators, two
+// logits of a token within rounding of each other came out in the other order in
+// one of some 150 calls, and with them whole rows of the gradients.)
+// A block's tiles of 16 tokens x 16 experts are shared out over the waves, so that
+// all four SIMDs issue MFMAs from 32 experts on: 8192 tokens, d = 2048, 64 experts
+// 36 us (32 with d split; 1913 with a thread's loop per logit), 5003 tokens, d =
+// 1536, 256 experts 83 (78; 5882), 256 tokens, d = 64, 8 experts 6.4 (7.1; 9.7).
+// x and W_r rows come to LDS by DMA as whole 128-byte pieces (a slice, 32 of d)
+// through a ring of NS stages of KS slices.  Chunk c (16 bytes) of row r sits at
+// chunk c ^ ((r >> 1) & 7).  VEC: rows are 16-byte aligned; otherwise the DMA
+// moves 4 bytes per lane.
+template <int EP, bool VEC>
+DEVI void logits_f32(const RouteFwdArgs& a, int t0, float* zl, int ldz) {
+  constexpr int KW = 32;                                // elements of a slice
+  constexpr int KS = EP == 256 ? 1 : EP == 128 ? 2 : 4;  // slices of a stage
+  constexpr int NS = 3;
+  constexpr int ROWS = RT_TOK + EP;                     // x rows, then W_r rows
+  constexpr int SLICE = ROWS * 128, STAGE = KS * SLICE;
+  constexpr int PIECES = STAGE / 1024;                  // of 8 rows
+  constexpr int PER_WAVE = (PIECES + RT_WAVES - 1) / RT_WAVES;
+  constexpr int PER = PER_WAVE * (VEC ? 1 : 4);         // DMA loads per wave and stage
+  constexpr int MT = EP >= 128 ? 2 : 1;                 // a wave's tiles of 16 tokens
+  constexpr int NT = EP == 256 ? 2 : 1;                 // and of 16 experts
+  __shared__ __attribute__((aligned(1024))) char ring[NS * STAGE];
+  const float* x = static_cast<const float*>(a.x);
+  const float* w = static_cast<const float*>(a.w);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n_stages = (a.d + KW * KS - 1) / (KW * KS);
+  // rows past the last token or expert repeat it (their results are not used)
+  auto row_at = [&](int r) {
+    return r < RT_TOK ? x + (size_t)min(t0 + r, a.T - 1) * a.d
+                      : w + (size_t)min(r - RT_TOK, a.E - 1) * a.d;
+  };
+  auto load = [&](int stage) {
+    char* st = ring + stage % NS * STAGE;
+#pragma unroll
+    for (int i = 0; i < PER_WAVE; ++i) {
+      // (the last waves of a stage that does not divide bring its first pieces again)
+      const int q = (wave * PER_WAVE + i) % PIECES;
+      const int r0 = q % (ROWS / 8) * 8;
+      const int k0 = (stage * KS + q / (ROWS / 8)) * KW;
+      char* dst = st + q * 1024;
+      if constexpr (VEC) {
+        const int r = r0 + (lane >> 3);
+        const int c = k0 + ((lane & 7) ^ ((r >> 1) & 7)) * 4;
+        route_dma<true>(c < a.d ? (const void*)(row_at(r) + c) : kRouteZeros, dst);
+      } else {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int r = r0 + 2 * u + (lane >> 5);
+          const int c = k0 + (((lane >> 2) & 7) ^ ((r >> 1) & 7)) * 4 + (lane & 3);
+          route_dma<false>(c < a.d ? (const void*)(row_at(r) + c) : kRouteZeros, dst + u * 256);
+        }
+      }
+    }
+  };
+  const int l16 = lane & 15, g4 = lane >> 4;
+  const int tok0 = MT == 2 ? 0 : (wave & 1) * 16;
+  const int exp0 = EP == 256 ? wave * 32 : EP == 128 ? wave * 16 : (wave >> 1) * 16;
+  const bool busy = exp0 < EP && exp0 < a.E;
+  // byte offset of element 4 m + g4 of a slice in row l16 of a 16-row tile
+  int off[8];
+#pragma unroll
+  for (int m = 0; m < 8; ++m) off[m] = l16 * 128 + ((m ^ ((l16 >> 1) & 7)) << 4) + g4 * 4;
+  f32x4_t acc[MT][NT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int p = 0; p < NS - 1; ++p)
+    if (p < n_stages) load(p);
+  for (int s = 0; s < n_stages; ++s) {
+    wait_vm_groups<PER, NS - 2>(n_stages - 1 - s);
+    __syncthreads();  // stage s is whole; everyone is done with stage s - 1
+    if (s + NS - 1 < n_stages) load(s + NS - 1);
+    if (!busy) continue;
+    const char* xl = ring + s % NS * STAGE + tok0 * 128;
+    const char* wl = ring + s % NS * STAGE + (RT_TOK + exp0) * 128;
+#pragma unroll
+    for (int q = 0; q < KS; ++q)
+#pragma unroll
+      for (int m = 0; m < 8; ++m) {
+        float xv[MT], wv[NT];
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+          xv[i] = *reinterpret_cast<const float*>(xl + q * SLICE + i * 2048 + off[m]);
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+          wv[j] = *reinterpret_cast<const float*>(wl + q * SLICE + j * 2048 + off[m]);
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+          for (int j = 0; j < NT; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[i], wv[j], acc[i][j], 0, 0, 0);
+      }
+  }
+  if (busy) {
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+      const int e = exp0 + 16 * j + l16;
+      if (e >= a.E) continue;
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int row = tok0 + 16 * i + 4 * g4 + r;
+          float v = acc[i][j][r];
+          if (a.bias) v += a.bias[e];
+          v *= a.inv_tau;
+          zl[row * ldz + e] = v;
+          if (a.logits && t0 + row < a.T) a.logits[(size_t)(t0 + row) * a.E + e] = v;
+        }
+    }
+  }
+  __syncthreads();
 }
 
 // Logit as read for selection: NaN ranks as -inf (some expert is always
@@ -489,9 +590,9 @@ DEVI void select_groups(const RouteFwdArgs& a, const float* zl, int t0, const in
 
 // Which logits path a block takes: STAGED4 / STAGED8 bf16, up to 64 experts
 // and d <= 64 * 4 / 64 * 8 * RT_WAVES; DIRECT bf16, up to 64 experts, longer d;
-// RING bf16 beyond 64 experts; RING_F32 fp32 with 16-byte aligned rows,
-// RING_F32_DWORD fp32 otherwise.
-enum RoutePath { STAGED4, STAGED8, DIRECT, RING, RING_F32, RING_F32_DWORD };
+// RING bf16 beyond 64 experts; F32 fp32 with 16-byte aligned rows, F32_DWORD
+// fp32 otherwise.
+enum RoutePath { STAGED4, STAGED8, DIRECT, RING, F32, F32_DWORD };
 
 template <int NEB, int PATH>
 __global__ __launch_bounds__(RT_THREADS) void route_fwd_kernel(RouteFwdArgs a) {
@@ -507,8 +608,8 @@ __global__ __launch_bounds__(RT_THREADS) void route_fwd_kernel(RouteFwdArgs a) {
   if constexpr (PATH == STAGED4) logits_mfma_staged<NEB, 4>(a, t0, zl, LDZ);
   else if constexpr (PATH == STAGED8) logits_mfma_staged<NEB, 8>(a, t0, zl, LDZ);
   else if constexpr (PATH == DIRECT) logits_mfma<NEB>(a, t0, zl, LDZ);
-  else if constexpr (PATH == RING) logits_ring<bf16_t, NEB, true>(a, t0, zl, LDZ);
-  else logits_ring<float, NEB, PATH == RING_F32>(a, t0, zl, LDZ);
+  else if constexpr (PATH == RING) logits_ring<NEB>(a, t0, zl, LDZ);
+  else logits_f32<NEB * 32, PATH == F32>(a, t0, zl, LDZ);
 
   if (a.k <= RT_KSEL) {
     static_assert(RT_TOK == 4 * RT_WAVES, "16 lanes per token in every wave");
@@ -1289,8 +1390,8 @@ hipError_t launch_route_fwd(const void* x, const void* w, const float* bias, int
 #define ROUTE_LAUNCH(N, P) MOE_TIMED("route_fwd", s, route_fwd_kernel<N, P><<<grid, RT_THREADS, 0, s>>>(a))
 #define ROUTE_F32(N)                       \
   do {                                     \
-    if (vec) ROUTE_LAUNCH(N, RING_F32);    \
-    else ROUTE_LAUNCH(N, RING_F32_DWORD);  \
+    if (vec) ROUTE_LAUNCH(N, F32);    \
+    else ROUTE_LAUNCH(N, F32_DWORD);  \
   } while (0)
 #define ROUTE_BF16(N)                                        \
   do {                                                       \

@@ -73,6 +73,45 @@ def test_router_forward(gpu_lib, dtype, T, d, E, k, aligned):
     np.testing.assert_allclose(host(wts), O.gate_weights(z, ref, "softmax"), rtol=2e-6, atol=1e-7)
 
 
+def _chain(x, w):
+    """x w^T in fp32, each logit one chain of fused multiply-adds in the order of d.
+    (A product and its sum in 64 mantissa bits, then rounded to 24: the fused
+    result, but for one step in some 2^40.)"""
+    x, w = x.astype(np.longdouble), w.astype(np.longdouble)
+    s = np.zeros((x.shape[0], w.shape[0]), np.float32)
+    for c in range(x.shape[1]):
+        s = (x[:, c, None] * w[None, :, c] + s).astype(np.float32)
+    return s
+
+
+# as FWD's, and one and two tiles of 16 experts, more stages than the ring holds
+@pytest.mark.parametrize("T,d,E,aligned", [(f[1], f[2], f[3], f[5]) for f in FWD if f[0] == "f32"]
+                         + [(50, 64, 8, True), (96, 516, 32, True), (33, 1030, 17, True),
+                            (40, 132, 128, False), (17, 900, 129, True)])
+def test_f32_logits_are_bitwise_a_serial_chain(gpu_lib, T, d, E, aligned):
+    """Another order of the sum moves logits by a rounding, and two of one token
+    that lie that close then change ranks: selections, gates and whole rows of the
+    gradients would depend on the kernel's split of d."""
+    say(f"[router-chain] T={T} d={d} E={E} aligned={aligned}")
+    g, x, w = _inputs(T, d, E, "f32")
+    bias = (g.standard_normal(E) * 0.1).astype(np.float32)
+    tx, tw_ = (dev(x, F32), dev(w, F32)) if aligned else (_unaligned(x), _unaligned(w))
+    z = _logits(tx, tw_, dev(bias, F32), 0.8)
+    want = (_chain(x, w) + bias) * np.float32(0.8)
+    assert np.array_equal(z.cpu().numpy(), want)
+
+
+def _logits(x, w, bias, tau):
+    (T, d), E = x.shape, w.shape[0]
+    z = torch.full((T, E), float("nan"), dtype=F32, device="cuda")
+    idx, loc = (torch.empty((T, 1), dtype=I32, device="cuda") for _ in range(2))
+    B.moe_route_mask(x, w, bias, B.dtype_code(x), T, d, E, 1, tau, B.GATES["softmax_topk"],
+                     torch.ones(E, dtype=torch.uint8, device="cuda"), z, idx,
+                     torch.empty((T, 1), dtype=F32, device="cuda"), loc)
+    torch.cuda.synchronize()
+    return z
+
+
 # dtype, T, d, E, k, gate, accumulate_dx, d_bias wanted, dW aligned
 BWD = [("f32", 70, 72, 10, 3, "softmax_topk", 1, True, True), ("f32", 256, 8, 16, 2, "sigmoid", 0, True, True),
        ("f32", 300, 200, 50, 4, "softmax", 0, True, True), ("f32", 600, 136, 100, 8, "softmax_topk", 1, True, False),
