@@ -294,18 +294,19 @@ DEVI void route_dma(const void* p, char* base) {
                  : "m0", "memory");
 }
 
-// bf16 logits of more than 64 experts.  The waves
-// form EG expert groups (32 experts each) x KG = 8 / EG groups of d slices: a
-// wave's 32 x 32 tile of (token, expert) runs over the slices kg, kg + KG, ...
-// of 128 bytes, so W_r is read once per block, each row by one wave, and only
-// KG partial sums are left to add.  (One wave for all experts of a d slice held
-// 128 accumulators at 256 experts and added them to LDS wave after wave:
-// 5003 tokens, d = 1536, 256 experts took 82 us.)
+// bf16 logits of more than 64 experts.  The waves form EG expert groups (32
+// experts each) x KG = 8 / EG groups of d slices: a wave's 32 x 32 tile of
+// (token, expert) runs over the slices kg, kg + KG, ... of 64, so W_r is read
+// once per block, each row by one wave.  (One wave for all experts of a d slice
+// held 128 accumulators at 256 experts and added them to LDS wave after wave:
+// 5003 tokens, d = 1536, 256 experts took 82 us, now 26, bound by each CU's read of
+// W_r (786 KB) from L2.)
+// The sums are those of the narrower paths, to the bit: slices s, s + 8, ... in
+// one accumulator, the same 16 of d in each MFMA, and the eight accumulators
+// added in order, so that a logit does not depend on how many experts there are
+// (a rounding's difference is enough to swap two ranks).
 // x and W_r rows go to LDS by DMA as whole 128-byte pieces through a ring of NS
 // stages.  Chunk c (16 bytes) of row r sits at chunk c ^ ((r >> 1) & 7).
-// Four accumulators in turn keep the chains of additions short.
-// The 256-expert case above now takes 31 us, bound by each CU's read of W_r
-// (786 KB) from L2.
 template <int EG>
 DEVI void logits_ring(const RouteFwdArgs& a, int t0, float* zl, int ldz) {
   constexpr int KG = RT_WAVES / EG;
@@ -316,8 +317,10 @@ DEVI void logits_ring(const RouteFwdArgs& a, int t0, float* zl, int ldz) {
   constexpr int NS = 3;
   constexpr int XP = KG >= 2 ? KG / 2 : 1;        // KiB of x per wave and stage
   constexpr int PER = 4 + XP;                     // DMA loads per wave and stage
-  static_assert(NS * STAGE >= KG * RT_TOK * EP * 4, "the partial sums reuse the ring");
-  __shared__ __attribute__((aligned(1024))) char ring[NS * STAGE];
+  constexpr int NA = RT_WAVES / KG;               // a wave's share of the 8 sums
+  constexpr int P = KG == 1 ? 1 : RT_WAVES;       // sums left to add through LDS
+  constexpr int PART = P * RT_TOK * EP * 4;
+  __shared__ __attribute__((aligned(1024))) char ring[NS * STAGE > PART ? NS * STAGE : PART];
   const bf16_t* x = static_cast<const bf16_t*>(a.x);
   const bf16_t* w = static_cast<const bf16_t*>(a.w);
   const int lane = threadIdx.x & 63;
@@ -344,34 +347,47 @@ DEVI void logits_ring(const RouteFwdArgs& a, int t0, float* zl, int ldz) {
       kib(x, t0 + 8 * (q & 3), a.T - 1, stage * KG + (q >> 2), st + W_BYTES + q * 1024);
     }
   };
-  f32x16_t acc[4] = {f32x16_t{}, f32x16_t{}, f32x16_t{}, f32x16_t{}};
+  f32x16_t acc[NA];
+#pragma unroll
+  for (int u = 0; u < NA; ++u) acc[u] = f32x16_t{};
   const int row = lane & 31, half = lane >> 5;
 #pragma unroll
   for (int p = 0; p < NS - 1; ++p)
     if (p < n_stages) load(p);
-  for (int s = 0; s < n_stages; ++s) {
-    wait_vm_groups<PER, NS - 2>(n_stages - 1 - s);
-    __syncthreads();  // stage s is whole; everyone is done with stage s - 1
-    if (s + NS - 1 < n_stages) load(s + NS - 1);
-    const char* wl = ring + s % NS * STAGE + wave * 4096;
-    const char* xl = ring + s % NS * STAGE + W_BYTES + kg * 4096;
+  for (int s0 = 0; s0 < n_stages; s0 += NA) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int o = row * 128 + (((2 * q + half) ^ ((row >> 1) & 7)) << 4);
-      acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8_t*>(xl + o),
-                                                       *reinterpret_cast<const bf16x8_t*>(wl + o),
-                                                       acc[q], 0, 0, 0);
+    for (int u = 0; u < NA; ++u) {
+      const int s = s0 + u;
+      if (s >= n_stages) break;
+      wait_vm_groups<PER, NS - 2>(n_stages - 1 - s);
+      __syncthreads();  // stage s is whole; everyone is done with stage s - 1
+      if (s + NS - 1 < n_stages) load(s + NS - 1);
+      const char* wl = ring + s % NS * STAGE + wave * 4096;
+      const char* xl = ring + s % NS * STAGE + W_BYTES + kg * 4096;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int o = row * 128 + (((4 * half + q) ^ ((row >> 1) & 7)) << 4);
+        acc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8_t*>(xl + o),
+                                                         *reinterpret_cast<const bf16x8_t*>(wl + o),
+                                                         acc[u], 0, 0, 0);
+      }
     }
   }
-  __syncthreads();  // the partial sums take the ring's place
+  __syncthreads();  // the sums take the ring's place
   float* part = reinterpret_cast<float*>(ring);
+  if constexpr (P == 1) {
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int i = (r >> 2) * 8 + half * 4 + (r & 3);
-    part[(kg * RT_TOK + i) * EP + eg * 32 + row] = (acc[0][r] + acc[1][r]) + (acc[2][r] + acc[3][r]);
+    for (int u = 1; u < NA; ++u) acc[0] += acc[u];
   }
+#pragma unroll
+  for (int u = 0; u < (P == 1 ? 1 : NA); ++u)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int i = (r >> 2) * 8 + half * 4 + (r & 3);
+      part[((u * KG + kg) * RT_TOK + i) * EP + eg * 32 + row] = acc[u][r];
+    }
   __syncthreads();
-  finish_logits<EP, KG>(a, t0, part, zl, ldz);
+  finish_logits<EP, P>(a, t0, part, zl, ldz);
 }
 
 // fp32 logits.  A logit is one chain of fused multiply-adds in the order of d,

@@ -101,6 +101,20 @@ def test_f32_logits_are_bitwise_a_serial_chain(gpu_lib, T, d, E, aligned):
     assert np.array_equal(z.cpu().numpy(), want)
 
 
+@pytest.mark.parametrize("T,d,E", [(70, 8, 65), (45, 200, 130), (33, 1544, 128), (20, 2056, 256),
+                                   (9, 4160, 100)])
+def test_bf16_logits_do_not_depend_on_the_number_of_experts(gpu_lib, T, d, E):
+    """More than 64 experts take another kernel path; it adds in the same order (see
+    above), so each 40 experts by themselves have bitwise the same logits."""
+    say(f"[router-experts] T={T} d={d} E={E}")
+    _, x, w = _inputs(T, d, E, "bf16")
+    tx, tw_ = dev(x, torch.bfloat16), dev(w, torch.bfloat16)
+    z = _logits(tx, tw_, None, 1.0)
+    for e in range(0, E, 40):
+        some = tw_[e:e + 40]
+        assert torch.equal(_logits(tx, some, None, 1.0), z[:, e:e + 40]), e
+
+
 def _logits(x, w, bias, tau):
     (T, d), E = x.shape, w.shape[0]
     z = torch.full((T, E), float("nan"), dtype=F32, device="cuda")
