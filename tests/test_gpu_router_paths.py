@@ -171,3 +171,42 @@ def test_router_backward(gpu_lib, dtype, T, d, E, k, gate, acc, want_bias, align
     want = ref["dx"] + (dx0 if acc else 0.0)
     errs["dx"] = assert_close("dx", host(dx), want, TOL["f32"] if dtype == "f32" else 2.0 ** -8)
     record_errors(f"router_bwd[{dtype} {T} {d} {E} {gate}]", errs)
+
+
+@pytest.mark.parametrize("gate", ["sigmoid", "softmax"])
+@pytest.mark.parametrize("T,d,E", [(70, 72, 10), (300, 136, 64), (300, 136, 65), (129, 72, 256)])
+def test_router_backward_keeps_infinities(gpu_lib, T, d, E, gate):
+    """bf16 layers that take dz in three parts: an infinite upstream gradient, x or
+    W_r gives the infinities and NaNs of plain sums of products, and no others."""
+    say(f"[router-inf] T={T} d={d} E={E} {gate}")
+    g, x, w = _inputs(T, d, E, "bf16")
+    k, inf = 3, np.inf
+    z = O.router_logits(x, w, 1.0).astype(np.float32)
+    idx = O.topk_select(z, k)
+    wts = O.gate_weights(z, idx, gate).astype(np.float32)
+    dtw = g.standard_normal((T, k)).astype(np.float32)
+    if gate == "sigmoid":  # (the others' dz of such a token is infinite or NaN throughout)
+        dtw[T // 2, 1], dtw[T - 1, 0] = inf, -inf
+    x[3, 5], x[T - 2, d - 1], w[E - 1, 9], w[E // 2, d - 7] = inf, -inf, inf, -inf
+    bf = torch.bfloat16
+    n_ws = B.moe_route_bwd_workspace_size(T, d, E)
+    dz, dw, db = (torch.empty(s, dtype=F32, device="cuda") for s in ((T, E), (E, d), (E,)))
+    dx = torch.empty((T, d), dtype=bf, device="cuda")
+    B.moe_route_bwd(dev(x, bf), dev(w, bf), B.MOE_BF16, T, d, E, k, 1.0, B.GATES[gate],
+                    torch.from_numpy(idx.astype(np.int32)).cuda(), dev(wts, F32), dev(z, F32),
+                    dev(dtw, F32), dz, dw, db, dx, 0, torch.empty(n_ws, dtype=torch.uint8, device="cuda"), n_ws)
+    torch.cuda.synchronize()
+    # (dz itself is elementwise and fp32: the sums are checked on the call's own)
+    z64 = host(dz)
+    assert np.isinf(z64).any() == (gate == "sigmoid")
+    with np.errstate(invalid="ignore"):
+        want = {"dW": (dw, z64.T @ x.astype(np.float64), TOL["f32"]), "d_bias": (db, z64.sum(0), TOL["f32"]),
+                "dx": (dx, z64 @ w.astype(np.float64), 2.0 ** -8)}
+    for name, (got, ref, tol) in want.items():
+        got = host(got)
+        assert np.array_equal(np.isnan(got), np.isnan(ref)), name
+        fin = np.isfinite(ref)
+        assert np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)]), name
+        assert name == "d_bias" or (fin.any() and np.isinf(ref).any()), name
+        if fin.any():
+            assert_close(name, got[fin], ref[fin], tol)
