@@ -1312,87 +1312,144 @@ hipError_t reduce_row_parts(const GemmArgs* args, int n_sets, hipStream_t s) {
   return hipSuccess;
 }
 
-// Which tiles a bf16 launch takes: the smallest estimate of its time.  256 x 256
-// tiles need the fewest operand bytes and run at the highest rate once they
-// fill the CUs; with few, ragged or short ones most CUs idle or each tile's
-// fill and epilogue weigh more than its k-steps, and smaller tiles (two or three
-// blocks per CU) finish earlier.  The sizes are known to the host only by
-// their bound; of a set with several groups, 0.6 of it is taken as present
-// (skip-token leaves 0.2 to 1 of the routes resident).
-// The constants are fits (us per 64-deep k-step and per tile, of a whole CU and
-// of a lone block) to the launches of twelve layers and expert blocks of 69 to
-// 16000 rows, d 64 to 2752, H 64 to 2816.  Measured, 256 x 256 / 64 x 128 / 64 x
-// 64: GU of 4096 rows, d = 1024, H = 2816, 8 groups: 76 / 103 / 130; its down
-// projection 48 + 10 (K parts and their sum) / 58 / 65; 2300 rows in 7 groups,
-// d = 960, H = 512: dX + dW 55 + 9 / 40 / 50; 300 rows, d = 1024, H = 1408, 4
-// groups: GU 30 / 19 / 17, dX + dW 37 + 7 / 38 / 31; the backward of a shared
-// expert of 6662 rows, H = 1152 beside 7 groups: dHh + dW_d 174 / 134 / 168 (its
-// dW_d tiles are few and long).
+// Which tiles a bf16 launch takes.  256 x 256 tiles need the fewest operand bytes
+// and run at the highest rate once they fill the CUs; with few, ragged or short
+// ones most CUs idle or each tile's fill and epilogue weigh more than its k-steps,
+// and smaller tiles (two or more blocks per CU) finish earlier.  The choice is by an
+// estimate of the launch's time in each size:
+//   max(longest tile, work / CUs + overlap * longest tile) + bytes / rate
+// with every constant (us per 64-deep k-step and per tile, TB/s) fitted to the
+// launches of 12000 drawn expert blocks (1 to 64 groups of 8 to 3000 rows, d 256 to
+// 4096, H 256 to 2816, with and without shared experts, both expert forms, nothing
+// in the caches); its median error is 4 % for the small tiles and 6 % for the large.
+//
+// The host knows a set's rows only by their bound.  A direct call and a
+// partitioned router fill it, skip-token leaves E_r / E of it, and a size that is
+// right at one end can lose a third at the other: so a size's estimates with all
+// rows present and with 0.4 of them are held against the best of each, and the size
+// whose worse ratio is the smallest is taken.  The small tiles have to win by 5 %:
+// they lose more where the estimate is wrong than they gain where it is close.
+// Over those launches, GU / down projection / dHh + dW_d / dX + dW_gu: the rule takes
+// 0.70 / 0.60 / 0.72 / 0.75 of the time of the large tiles alone (the fastest size of
+// each would take 0.68 / 0.58 / 0.71 / 0.73), and 0.5 / 0.5 / 1.0 / 0.5 % of them over
+// 10 % longer; 1.1 / 0.5 / 2.4 / 1.1 % without the 5 %, 3.4 / 0.8 / 1.1 / 3.8 % by
+// an estimate at 0.6 of the rows alone, without the bytes (200 rows in each of 16
+// groups, d = 2048, H = 1408, forward: 106 us, but 143 by that estimate).
+// In us, 256 x 256 / 64 x 128 / 64 x 64 / 32 x 64: GU of 4096 rows in 8 groups, d =
+// 1024, H = 2816: 71 / 101 / 126 / 230, its down projection 48 + 10 (K parts and their
+// sum) / 58 / 64 / 95; up projection of 12004 rows in 12 groups, d = 768, H = 704: 29 /
+// 31 / 36 / 66; 256 rows in 8 groups, d = 1024, H = 2816: GU 33 / 24 / 22 / 30, dX + dW
+// 74 + 9 with K parts, 142 without / 115 / 86; 72 rows in 16 groups and 48 shared, d =
+// 2048, H = 1408 and 2816: down projection 51 + 9 / 47 / 31 / 27.
 struct TileCost {
+  TileSize size;
   int bm, bn;
-  double step, tile;            // of a CU's time
-  double lone_step, lone_tile;  // alone on a CU
+  double step, lone_step;      // of a CU's time; of a lone block
+  double swiglu, linear, dw;   // per tile: SwiGLU (SiLU) epilogues, others, weight gradients
+  double overlap;
+  double rate, dw_rate;        // operands and rows; fp32 weight gradients
 };
-constexpr TileCost kTileCost[] = {{256, 256, 1.45, 6.0, 1.45, 6.0},
-                                  {64, 128, 0.35, 1.6, 0.55, 6.0},
-                                  {64, 64, 0.25, 1.1, 0.45, 5.0}};
+constexpr TileCost kTileCost[] = {
+    {TILE_256x256, 256, 256, 1.27, 1.27, 5.0, 2.0, 5.4, 0.30, 6.0, 9.0},
+    {TILE_64x128, 64, 128, 0.30, 0.82, 1.95, 0.75, 0.4, 0.35, 5.4, 6.5},
+    {TILE_64x64, 64, 64, 0.20, 0.395, 1.45, 0.75, 0.5, 0.33, 5.4, 8.0},
+    {TILE_32x64, 32, 64, 0.16, 0.275, 1.75, 1.2, 0.0, 0.40, 5.6, 8.0}};
 
+// Estimates (us) of a launch: as it is, and - large tiles of the linear kinds - when
+// its long tiles may be cut into K parts, with their rows' sum launched after it.
 struct Estimate {
-  double us;
-  bool parts;  // the long tiles outlast the others' work: cut them into K parts
+  double us, parts;
 };
+// present: share of the bound on a set's rows.  split: K split of each of sb
+// (large tiles).
 Estimate estimate(const TileCost& c, int ka, const GemmArgs* sa, int na, const GemmArgs* sb, int nb,
-                  bool parts) {
-  double sum = 0, longest = 0, most_parts = 0;
+                  double present, const int* split) {
+  const bool large = c.size == TILE_256x256;
+  const bool linear = ka == DOWN_FWD || ka == DX_BWD;
+  auto rows_of = [&](const GemmArgs& a) {  // per group
+    return a.n_groups == 1 ? (double)a.cap : present * a.cap / a.n_groups;
+  };
+  double work = 0, steps_sum = 0, tiles_sum = 0, long_m = 0, long_k = 0, bytes = 0, dw_bytes = 0;
   for (int q = 0; q < na + nb; ++q) {
     const GemmArgs& a = q < na ? sa[q] : sb[q - na];
     if (a.n_groups == 0 || a.cap == 0) continue;
     const bool mrag = q < na;  // every second kind of a launch is ragged in K
-    const double rows = a.n_groups == 1 ? a.cap : 0.6 * a.cap / a.n_groups;  // per group
-    double m = mrag ? rows / c.bm : (double)ceil_div(a.M, c.bm);
-    if (mrag) m = a.n_groups == 1 ? std::ceil(m) : std::max(1.0, m + 0.5);
+    const double rows = rows_of(a), total = rows * a.n_groups;
+    const int S = mrag || !large ? 1 : split[q - na];
+    // groups vary by about the root of their rows
+    const double vary = a.n_groups == 1 ? 0.0 : std::sqrt(rows);
+    const double m = mrag ? 0.5 * (std::ceil(std::max(1.0, rows - vary) / c.bm) +
+                                   std::ceil((rows + vary) / c.bm))
+                          : (double)ceil_div(a.M, c.bm) * S;
     const double tiles = m * a.n_groups * ceil_div(a.N, c.bn);
-    const double steps = std::ceil((mrag ? a.K : rows) / 64.0);
-    sum += tiles * (steps * c.step + c.tile);
-    const double lone = steps * c.lone_step + c.lone_tile;
-    // K parts cut the long tiles of the linear kinds
-    if (parts && mrag && (ka == DOWN_FWD || ka == DX_BWD)) most_parts = std::max(most_parts, lone);
-    else longest = std::max(longest, lone);
+    const double steps = std::max(1.0, std::ceil((mrag ? a.K : rows / S) / 64.0));
+    const double tile = !mrag ? c.dw : linear ? c.linear : c.swiglu;
+    work += tiles * (steps * c.step + tile);
+    steps_sum += tiles * steps;
+    tiles_sum += tiles;
+    double& longest = mrag ? long_m : long_k;
+    longest = std::max(longest, steps * c.lone_step + tile);
+    bytes += total * ((double)a.N + (mrag ? a.K : a.M));  // bf16 rows, half of them from L2
+    if (mrag) bytes += 2.0 * a.n_groups * a.N * a.K;
+    else dw_bytes += 4.0 * a.n_groups * a.M * a.N * (S > 1 ? 1 + 2 * S : 1);
   }
-  sum /= num_cus();
-  const double t = std::max(longest, sum + 0.3 * longest);
-  // (in a merged launch the long tiles run beside many short ones, slower than
-  // alone; 20: the partial rows, their sum and its launch).  Mid-size dX + dW_gu
-  // 156 + 9 us with parts, 183 without; fine-grained down projection, sigma-MoE dX
-  // and the like level, and a launch less without.
-  const double uncut = std::max(t, (nb ? 1.35 : 1.0) * most_parts), cut = std::max(t, sum * 4 / 3) + 20;
-  return {std::min(uncut, cut), cut < uncut};
+  const double per_cu = work / num_cus();
+  const double longest = std::max(long_m, long_k);
+  double t = std::max(longest, per_cu + c.overlap * longest);
+  if (large && nb > 0) t = std::max(per_cu + c.overlap * longest, 0.9 * long_m + 0.6 * long_k);
+  // one block per CU: whole rounds of tiles
+  if (large && nb == 0 && tiles_sum > 0)
+    t = std::max(longest, std::ceil(tiles_sum / num_cus()) * work / tiles_sum);
+  const double mem = bytes / c.rate * 1e-6, dw_mem = dw_bytes / c.dw_rate * 1e-6;
+  Estimate e{t + mem + dw_mem, INFINITY};
+  if (!large || !linear) return e;
+  // the kernel cuts a tile longer than 4/3 of the average block's work
+  double part_bytes = 0;
+  for (int q = 0; q < na; ++q) {
+    const GemmArgs& a = sa[q];
+    if (a.n_groups == 0 || a.cap == 0) continue;
+    const double S = std::min((double)row_parts_max(1, a.cap, a.N),
+                              std::ceil(std::ceil(a.K / 64.0) / (4.0 / 3.0 * steps_sum / num_cus())));
+    if (S > 1) part_bytes += 8.0 * S * rows_of(a) * a.n_groups * a.N;
+  }
+  if (part_bytes == 0) e.parts = e.us + 5.0;  // the sum's launch, which finds one part
+  else
+    e.parts = (nb > 0 ? 0.85 * long_k + 0.73 * per_cu + 2.0 * dw_mem : 2.0 * per_cu) + 0.35 * mem +
+              0.9 * part_bytes / 5.0 * 1e-6 + 9.0;
+  return e;
 }
 
 // parts: in, whether the launch may cut long tiles into K parts; out, whether it
 // should (a launch that may has its partial rows' sum launched after it).
-TileSize choose_tiles(int ka, const GemmArgs* sa, int na, const GemmArgs* sb, int nb, bool* parts) {
+TileSize choose_tiles(int ka, const GemmArgs* sa, int na, const GemmArgs* sb, int nb,
+                      const int* split, bool* parts) {
   const bool may = *parts;
   *parts = false;
-  // about 32 rows per group or fewer: the weights' stream is all, with the
-  // deepest ring (48 tokens over the fine-grained experts: GU 51, down projection
-  // 29 us against 53 and 32 with 64 x 64 tiles, 57 and 49 + 5 with 256 x 256;
-  // 58 rows per group: 542 us against 396 with 64 x 128, two of whose rows of
-  // tiles would read each weight again)
-  if (nb == 0) {
-    bool few = true;
-    for (int q = 0; q < na; ++q)
-      few = few && (sa[q].n_groups == 1 ? sa[q].cap <= 64 : 0.6 * sa[q].cap <= 32.0 * sa[q].n_groups);
-    if (few) return TILE_32x64;
+  constexpr int kSizes = 4, kCand = kSizes + 1;  // the last: large tiles with K parts
+  constexpr double kPresent[2] = {1.0, 0.4};
+  double us[kCand][2], best[2] = {INFINITY, INFINITY};
+  for (int p = 0; p < 2; ++p) {
+    us[kSizes][p] = INFINITY;
+    for (int i = 0; i < kSizes; ++i) {
+      us[i][p] = INFINITY;
+      if (kTileCost[i].size == TILE_32x64 && nb > 0) continue;
+      const Estimate e = estimate(kTileCost[i], ka, sa, na, sb, nb, kPresent[p], split);
+      us[i][p] = (e.us + 4.0) * (i == 0 ? 1.0 : 1.05);  // 4: the launch itself
+      if (i == 0 && may) us[kSizes][p] = e.parts + 4.0;
+    }
+    for (int i = 0; i < kCand; ++i) best[p] = std::min(best[p], us[i][p]);
   }
-  const Estimate big = estimate(kTileCost[0], ka, sa, na, sb, nb, may);
-  const double mid = estimate(kTileCost[1], ka, sa, na, sb, nb, false).us;
-  const double small = estimate(kTileCost[2], ka, sa, na, sb, nb, false).us;
-  if (big.us <= mid && big.us <= small) {
-    *parts = big.parts;
-    return TILE_256x256;
+  int pick = 0;
+  double least = INFINITY;
+  for (int i = 0; i < kCand; ++i) {
+    const double worse = std::max(us[i][0] / best[0], us[i][1] / best[1]);
+    if (worse < least) {
+      least = worse;
+      pick = i;
+    }
   }
-  return mid <= small ? TILE_64x128 : TILE_64x64;
+  *parts = pick == kSizes;
+  return *parts ? TILE_256x256 : kTileCost[pick].size;
 }
 
 }  // namespace
@@ -1442,7 +1499,7 @@ hipError_t launch_ffn_fwd_sets(const moe_ffn_set* sets, int n_sets, int bf16, in
   }
   const int first = silu ? UP_FWD : GU_FWD;
   bool parts = false;
-  TileSize size = bf16 ? choose_tiles(first, g, n_sets, nullptr, 0, &parts) : TILE_64x128;
+  TileSize size = bf16 ? choose_tiles(first, g, n_sets, nullptr, 0, nullptr, &parts) : TILE_64x128;
   hipError_t e;
   if (bf16 && size == TILE_256x256)
     e = silu ? run_gemm_bf16<UP_FWD, UP_FWD>(g, n_sets, nullptr, 0, s, nullptr)
@@ -1451,7 +1508,7 @@ hipError_t launch_ffn_fwd_sets(const moe_ffn_set* sets, int n_sets, int bf16, in
     e = run_gemm_tile(bf16, first, first, g, n_sets, nullptr, 0, size, s);
   if (e != hipSuccess) return e;
   parts = ws != nullptr;
-  if (bf16) size = choose_tiles(DOWN_FWD, o, n_sets, nullptr, 0, &parts);
+  if (bf16) size = choose_tiles(DOWN_FWD, o, n_sets, nullptr, 0, nullptr, &parts);
   if (!bf16 || size != TILE_256x256)
     return run_gemm_tile(bf16, DOWN_FWD, DOWN_FWD, o, n_sets, nullptr, 0, size, s);
   if (parts) assign_row_parts(o, sets, n_sets, bf16, d, static_cast<char*>(ws));
@@ -1505,18 +1562,22 @@ hipError_t launch_ffn_bwd_sets(const moe_ffn_set* sets, int n_sets, int bf16, in
   // then dX with dW_gu (both read dG/dU)
   TileSize size1 = TILE_64x128, size2 = TILE_64x128;
   bool parts = ws != nullptr;
+  int split1[2] = {1, 1}, split2[2] = {1, 1};
   if (bf16) {
+    for (int i = 0; ws && i < n_sets; ++i) {
+      split1[i] = ksplit_factor(bf16, wd[i].M, wd[i].N, sets[i], bwd_launch_tiles(sets, n_sets, d, false));
+      split2[i] = ksplit_factor(bf16, wgu[i].M, wgu[i].N, sets[i], bwd_launch_tiles(sets, n_sets, d, true));
+    }
     bool none = false;
-    size1 = choose_tiles(silu ? DH_BWD : DHH_BWD, hh, n_sets, wd, n_sets, &none);
-    size2 = choose_tiles(DX_BWD, dx, n_sets, wgu, n_sets, &parts);
+    size1 = choose_tiles(silu ? DH_BWD : DHH_BWD, hh, n_sets, wd, n_sets, split1, &none);
+    size2 = choose_tiles(DX_BWD, dx, n_sets, wgu, n_sets, split2, &parts);
   }
   const bool large1 = bf16 && size1 == TILE_256x256, large2 = bf16 && size2 == TILE_256x256;
   // a single large group's dW split by rows, in the large tiles
   for (int i = 0; ws && i < n_sets; ++i) {
     for (GemmArgs* g : {&wd[i], &wgu[i]}) {
       if (!(g == &wd[i] ? large1 : large2)) continue;
-      const int S = ksplit_factor(bf16, g->M, g->N, sets[i],
-                                  bwd_launch_tiles(sets, n_sets, d, g == &wgu[i]));
+      const int S = g == &wd[i] ? split1[i] : split2[i];
       if (S <= 1) continue;
       const size_t n = (size_t)g->M * g->N;
       red[n_red++] = Reduce{static_cast<float*>(g->C), reinterpret_cast<const float*>(part), S, n};

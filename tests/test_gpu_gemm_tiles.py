@@ -115,3 +115,45 @@ def test_ffn_tile_sizes(gpu_lib, name):
                 else:
                     errs[f"{key}.{i}.{r}"] = assert_close(f"{key}[{r}]", value[r], w, tol)
     record_errors(f"gemm_tiles[{name}]", errs)
+
+
+# groups, rows of each, d, H, direction, kernels that must run and must not: where
+# the wrong size took a fifth to four fifths longer than the right one
+CHOICES = [
+    (16, 200, 2048, 1408, "fwd", {"gemm_gu_fwd", "gemm_down_fwd"}, {"gemm_gu_fwd_tile", "gemm_down_fwd_tile"}),
+    (8, 300, 4096, 2048, "fwd", {"gemm_gu_fwd", "gemm_down_fwd"}, {"gemm_gu_fwd_tile", "gemm_down_fwd_tile"}),
+    (8, 32, 1024, 2816, "bwd", {"gemm_dx_dwgu", "splitk_rows_reduce"}, {"gemm_dx_dwgu_tile"}),
+    (12, 80, 768, 704, "fwd", {"gemm_gu_fwd_tile", "gemm_down_fwd_tile"}, {"gemm_gu_fwd", "gemm_down_fwd"}),
+    (12, 80, 768, 704, "bwd", {"gemm_dhh_dwd_tile", "gemm_dx_dwgu_tile"}, {"gemm_dhh_dwd", "gemm_dx_dwgu"}),
+]
+
+
+@pytest.mark.parametrize("G,rows,d,H,way,runs,not_", CHOICES)
+def test_choice_where_every_row_is_present(gpu_lib, G, rows, d, H, way, runs, not_):
+    """A direct call fills the bound on its rows: the estimate has to hold there too."""
+    say(f"[gemm-choice] {G} x {rows} rows d={d} H={H} {way}")
+    n, bf = G * rows, torch.bfloat16
+
+    def new(*shape, dt=bf):
+        return torch.zeros(shape, dtype=dt, device="cuda")
+
+    off = (torch.arange(G + 1, dtype=torch.int32) * rows).cuda()
+    t = dict(yp=new(n, d))  # (a set holds addresses only)
+    if way == "bwd":
+        t.update(dyp=new(n, d), dgu=new(n, 2 * H), dxp=new(n, d), dw_gate_up=new(G, 2 * H, d, dt=F32),
+                 dw_down=new(G, d, H, dt=F32))
+    xp, w1, w2, gu, h = new(n, d), new(G, 2 * H, d), new(G, d, H), new(n, 2 * H), new(n, H)
+    s = B.ffn_set(xp, w1, w2, off, n, H, G, gu, h, **t)
+    size = B.moe_grouped_ffn_fwd_workspace_size if way == "fwd" else B.moe_grouped_ffn_bwd_workspace_size
+    n_ws = size([s], B.MOE_BF16, d)
+    ws = new(max(1, n_ws), dt=torch.uint8)
+    B.moe_timing_enable(64)
+    try:
+        if way == "fwd":
+            B.moe_grouped_ffn_fwd_sets([s], B.MOE_BF16, d, ws if n_ws else None, n_ws)
+        else:
+            B.moe_grouped_ffn_bwd_sets([s], B.MOE_BF16, d, 0, ws, n_ws)
+        ran = set(B.moe_timing_collect())
+    finally:
+        B.moe_timing_enable(0)
+    assert runs <= ran and not (not_ & ran), ran
