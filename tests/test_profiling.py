@@ -74,6 +74,24 @@ def test_every_kernel_of_the_library_has_a_timing_name():
         assert P.timing_name(f"void moe::(anonymous namespace)::{n}<0, 0>(x)") is not None, n
 
 
+def test_symbols_of_a_trace_have_timing_names():
+    """Every kernel of the library that the committed trace lists, in the profiler's
+    spelling: its demangler garbles bf16 template arguments (`<bool _Accum, int, E,
+    ...>`), and a kernel without a name would drop out of the summaries."""
+    import os
+    path = os.path.join(os.path.dirname(P.PKG), "profiles", "kernels_measured-cases.txt")
+    symbols = [line.split(" us ", 1)[1].strip() for line in open(path) if " us " in line]
+    ours = [s for s in symbols if "moe" in s]
+    assert len(ours) > 50
+    for s in ours:
+        assert P.timing_name(s) is not None, s
+    garbled = "void moe::(anonymous namespace)::gemm_tile_kernel<bool _Accum, int, E, {}, 2, 4, 2>(x)"
+    assert P.timing_name(garbled.format(1)) == "gemm_down_fwd_tile"
+    assert P.timing_name(garbled.format(5)) == "gemm_dx_dwgu_tile"
+    assert P.timing_name("_ZN3moe12_GLOBAL__N_116gemm_tile_kernelIDF16bLi7ELi4ELi2ELi4ELi2EEEvNS_10GemmLaunchE") \
+        == "gemm_dh_dwd_tile"
+
+
 def test_mangled_names_shorten_to_the_kernel():
     assert P._mangled_kernel_name(
         "_ZN3moe12_GLOBAL__N_123combine_bwd_rows_kernelIDF16bEEvPKT_S4_") == "combine_bwd_rows_kernel"
