@@ -171,10 +171,9 @@ def test_full_size_expert_delta(gpu_lib, wl):
 
 @pytest.mark.parametrize("wl", [1, 2])
 def test_full_size_layer_is_deterministic(gpu_lib, wl):
-    """Three steps of the mid-size layer (its down projection and dX cut into K
-    parts) and of the fine-grained one (shared expert, merged backward
-    launches) give bit-identical outputs and gradients, whichever blocks the
-    dynamically dealt tiles ran on."""
+    """Three steps of the mid-size layer (its dX cut into K parts) and of the
+    fine-grained one (shared expert, merged backward launches) give bit-identical
+    outputs and gradients, whichever blocks the dynamically dealt tiles ran on."""
     say(f"[determinism] workload {wl}: inputs")
     inp = I.make_layer_inputs(wl)
     L, _ = run_gpu_layer(inp)

@@ -5,7 +5,8 @@ its time.  The timing names tell the large tiles from the small ones; the
 shapes here reach every kind in both, with group sizes at the edges of the
 tile heights (empty, 1, 31..33, 63..65, 127..129, 255..257, 511, 513 rows),
 partial column tiles, ragged K of the weight gradients, both expert forms, one
-and two sets, with and without a workspace, and accumulated gradients.  The
+and two sets, with and without a workspace, accumulated gradients, reductions cut
+into parts (by rows, by K) and a first group that does not start at row 0.  The
 tolerance is the bf16 layers' own, normwise.
 """
 from __future__ import annotations
@@ -37,7 +38,25 @@ CASES = {
     "many-uneven-groups": ([[5 * (i % 17) if i % 9 else 300 for i in range(70)]], 192, [192],
                            "swiglu", True, 1, "0000"),
     "many-groups": ([[5 * (i % 17) for i in range(70)]], 64, [64], "swiglu", True, 0, "0000"),
+    # the same in the large tiles, whose uneven groups are shared out by time
+    "many-uneven-groups-large": ([[600 if i % 9 == 0 else 190 + i for i in range(70)]], 512, [448],
+                                 "swiglu", True, 0, "1111"),
+    # one group's weight gradients cut by rows into parts, and their sum
+    "one-group-split": ([[4100]], 256, [256], "swiglu", True, 0, "0011"),
+    "one-group-split-silu-acc": ([[4100]], 256, [256], "silu", True, 1, "0011"),
+    # few tiles with a long reduction: the down projection and dX in K parts
+    "k-parts": ([[300, 0, 109]], 192, [2048], "swiglu", True, 0, "0101"),
+    "k-parts-shared": ([[100, 0, 270, 10], [132]], 256, [2432, 4864], "swiglu", True, 1, "0101"),
+    # the first group does not start at row 0
+    "lead-small": ([[63, 64, 0, 129, 144]], 320, [704], "silu", True, 0, "0000"),
+    "lead-large": ([LARGE], 2240, [1984], "swiglu", True, 0, "1111"),
+    "lead-k-parts": ([[300, 0, 109]], 192, [2048], "silu", True, 1, "0101"),
 }
+LEAD = {"lead-small": 40, "lead-large": 37, "lead-k-parts": 5}  # rows before the first group
+# other kernels that have to run
+ALSO = {"one-group-split": "splitk_reduce", "one-group-split-silu-acc": "splitk_reduce",
+        "k-parts": "splitk_rows_reduce", "k-parts-shared": "splitk_rows_reduce",
+        "lead-k-parts": "splitk_rows_reduce"}
 
 
 @pytest.mark.parametrize("name", sorted(CASES))
@@ -57,8 +76,9 @@ def test_ffn_tile_sizes(gpu_lib, name):
     sets, state = [], []
     for sizes, H in zip(set_sizes, Hs):
         G, n = len(sizes), sum(sizes)
-        cap = n + 70 if len(sizes) > 1 else n  # rows past the groups stay untouched
-        off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+        lead = LEAD.get(name, 0)
+        cap = lead + n + 70 if len(sizes) > 1 else n  # rows outside the groups stay untouched
+        off = (lead + np.concatenate([[0], np.cumsum(sizes)])).astype(np.int32)
         s = dict(sizes=sizes, H=H, n=n, off=off, xp=draw(cap, d), dyp=draw(cap, d),
                  w1=draw(G, r1 * H, d, std=d ** -0.5), w2=draw(G, d, H, std=H ** -0.5))
         for key, shape in (("dw1", (G, r1 * H, d)), ("dw2", (G, d, H))):
@@ -89,23 +109,26 @@ def test_ffn_tile_sizes(gpu_lib, name):
     got = "".join("1" if k in ran else "0" for k in kinds)
     assert all((k in ran) != (k + "_tile" in ran) for k in kinds), ran
     assert got == large, f"large tiles in {got}, expected {large}"
+    assert name not in ALSO or ALSO[name] in ran, ran
 
     tol, errs = TOL["bf16"], {}
     for i, (s, t) in enumerate(state):
-        n, H = s["n"], s["H"]
-        f = O.grouped_ffn_fwd(s["xp"][:n], s["off"], s["w1"], s["w2"], expert)
-        b = O.grouped_ffn_bwd(s["dyp"][:n], s["xp"][:n], f["G"], f["U"], f["Hh"], s["off"],
+        H, lead = s["H"], int(s["off"][0])
+        at, off = slice(lead, lead + s["n"]), s["off"] - lead  # the groups' rows
+        f = O.grouped_ffn_fwd(s["xp"][at], off, s["w1"], s["w2"], expert)
+        b = O.grouped_ffn_bwd(s["dyp"][at], s["xp"][at], f["G"], f["U"], f["Hh"], off,
                               s["w1"], s["w2"], expert)
         gu, dgu = host(t["gu"]), host(t["dgu"])
-        pairs = [("G", gu[:n, :H], f["G"]), ("h", host(t["h"])[:n], f["Hh"]),
-                 ("yp", host(t["yp"])[:n], f["Y"]), ("dG", dgu[:n, :H], b["dG"]),
-                 ("dxp", host(t["dxp"])[:n], b["dXp"])]
+        pairs = [("G", gu[at, :H], f["G"]), ("h", host(t["h"])[at], f["Hh"]),
+                 ("yp", host(t["yp"])[at], f["Y"]), ("dG", dgu[at, :H], b["dG"]),
+                 ("dxp", host(t["dxp"])[at], b["dXp"])]
         if expert == "swiglu":
-            pairs += [("U", gu[:n, H:], f["U"]), ("dU", dgu[:n, H:], b["dU"])]
+            pairs += [("U", gu[at, H:], f["U"]), ("dU", dgu[at, H:], b["dU"])]
         for key, value, want in pairs:
             errs[f"{key}{i}"] = assert_close(key, value, want, tol)
         for key in ("gu", "h", "yp", "dgu", "dxp"):
-            assert torch.isnan(t[key][n:]).all(), f"{key}: a row past the groups was written"
+            assert torch.isnan(t[key][at.stop:]).all(), f"{key}: a row past the groups was written"
+            assert torch.isnan(t[key][:lead]).all(), f"{key}: a row before the groups was written"
         for key, want in (("dw1", b["dW_gate_up"]), ("dw2", b["dW_down"])):
             value = host(t[key])
             for r, sz in enumerate(s["sizes"]):

@@ -3,14 +3,13 @@ oracle, with the group sizes chosen around the GEMM tile edges.
 
 The layer tests reach only the group sizes that routing happens to give.
 Here they are set directly: empty groups (also first and last), one row, and
-one below, at and above 128 rows (a wave pair's share of a tile) and the
-256-row tile height; hidden and model widths that leave a partial 256-wide column tile;
-K extents (d, H, 2H) of one to several k-steps of 32 and 64 and ragged token
-counts for the weight-gradient kinds; the backward both without a workspace
-(static tile dealing, no split) and with one (dynamic dealing, split-K of a
-single large group, summed by splitk_reduce); with workspaces, launches with
-far fewer tiles than CUs, whose down projection and dX cut their reduction
-into parts (summed by splitk_rows_reduce).  Both expert forms.
+one below, at and above 128 and 256 rows; hidden and model widths that leave a
+partial column tile; K extents (d, H, 2H) of one to several k-steps and ragged
+token counts for the weight-gradient kinds; the backward both without a workspace
+and with one.  Both expert forms.  Which tiles a launch takes is the library's
+choice: most of these take the small ones; the single large group's backward
+takes the large ones with its rows cut into parts, and few-tiles-long-k's dX cuts
+its reduction.  test_gpu_gemm_tiles names the kernels that each of its shapes runs.
 
 Every output is compared with the oracle (Sec. 3.2 expert FFN per resident
 expert, App. B.3.1 for the SiLU form) at the bf16 tolerance, normwise.
@@ -45,8 +44,7 @@ CASES = {
     # gradients), so the load ring is never full
     "short-k": ([33, 64, 65, 96, 97, 0, 1, 31, 32], 64, 64, "swiglu", True, 0),
     "short-k-silu": ([33, 64, 65, 96, 97, 0, 1, 31, 32], 64, 64, "silu", False, 0),
-    # far fewer output tiles than CUs with long reductions: the down
-    # projection and dX cut K into parts (fp32 partial rows, then summed)
+    # far fewer output tiles than CUs with long reductions
     "few-tiles-long-k": ([300, 0, 257, 511], 256, 2048, "swiglu", True, 0),
     "few-tiles-long-k-silu": ([129, 640], 512, 1536, "silu", True, 1),
 }
