@@ -63,26 +63,12 @@ DEVI void dma16(const void* uniform, unsigned off, char* base) {
                : "m0", "memory");
 }
 
-// Four consecutive elements.
-template <class T>
-struct Vec4;
-template <>
-struct Vec4<float> {
-  typedef f32x4_t type;
-};
-template <>
-struct Vec4<bf16_t> {
-  typedef bf16x4_t type;
-};
-template <class T>
+// Four consecutive fp32, eight bf16.
 DEVI void put4(void* base, size_t i, f32x4_t v) {
-  *reinterpret_cast<typename Vec4<T>::type*>(static_cast<T*>(base) + i) =
-      __builtin_convertvector(v, typename Vec4<T>::type);
+  *reinterpret_cast<f32x4_t*>(static_cast<float*>(base) + i) = v;
 }
-template <class T>
 DEVI f32x4_t get4(const void* base, size_t i) {
-  return __builtin_convertvector(
-      *reinterpret_cast<const typename Vec4<T>::type*>(static_cast<const T*>(base) + i), f32x4_t);
+  return *reinterpret_cast<const f32x4_t*>(static_cast<const float*>(base) + i);
 }
 DEVI void put8(void* base, size_t i, bf16x8_t v) {
   *reinterpret_cast<bf16x8_t*>(static_cast<bf16_t*>(base) + i) = v;
@@ -90,12 +76,6 @@ DEVI void put8(void* base, size_t i, bf16x8_t v) {
 DEVI bf16x8_t get8(const void* base, size_t i) {
   return *reinterpret_cast<const bf16x8_t*>(static_cast<const bf16_t*>(base) + i);
 }
-// v as it is stored in T
-template <class T>
-DEVI f32x4_t rounded(f32x4_t v) {
-  return __builtin_convertvector(__builtin_convertvector(v, typename Vec4<T>::type), f32x4_t);
-}
-
 // bf16: hardware exp2 and reciprocal (about 1 ulp of fp32), as in the large tiles
 template <class T>
 DEVI float sigmoid_t(float g) {
@@ -117,34 +97,34 @@ struct TileAt {
   int g, row0, rows, m0, tile_n;
 };
 
-// Four consecutive output columns n .. n + 3 of tile row i (both in range).
-template <class T, int KIND>
+// Four consecutive fp32 output columns n .. n + 3 of tile row i (both in range):
+// rows of fp32 layers, weight gradients of either type.
+template <int KIND>
 DEVI void store_cols(const GemmArgs& a, const TileAt& t, int i, int n, f32x4_t v) {
   if constexpr (Kind<KIND>::MRAG) {
     const size_t m = (size_t)(t.row0 + i);
-    v = rounded<T>(v);
     if constexpr (KIND == DHH_BWD) {
       // dG = dHh U silu'(G), dU = dHh silu(G)
-      const f32x4_t G = get4<T>(a.aux, m * 2 * a.H + n), U = get4<T>(a.aux, m * 2 * a.H + a.H + n);
+      const f32x4_t G = get4(a.aux, m * 2 * a.H + n), U = get4(a.aux, m * 2 * a.H + a.H + n);
       f32x4_t dG, dU;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        dG[e] = v[e] * U[e] * dsilu_t<T>(G[e]);
-        dU[e] = v[e] * silu_t<T>(G[e]);
+        dG[e] = v[e] * U[e] * dsilu_t<float>(G[e]);
+        dU[e] = v[e] * silu_t<float>(G[e]);
       }
-      put4<T>(a.C, m * 2 * a.H + n, dG);
-      put4<T>(a.C, m * 2 * a.H + a.H + n, dU);
+      put4(a.C, m * 2 * a.H + n, dG);
+      put4(a.C, m * 2 * a.H + a.H + n, dU);
     } else if constexpr (KIND == DH_BWD) {
-      const f32x4_t A = get4<T>(a.aux, m * a.H + n);
+      const f32x4_t A = get4(a.aux, m * a.H + n);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] *= dsilu_t<T>(A[e]);
-      put4<T>(a.C, m * a.ldc + n, v);
+      for (int e = 0; e < 4; ++e) v[e] *= dsilu_t<float>(A[e]);
+      put4(a.C, m * a.ldc + n, v);
     } else {
-      put4<T>(a.C, m * a.ldc + n, v);
+      put4(a.C, m * a.ldc + n, v);
       if constexpr (KIND == UP_FWD) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = silu_t<T>(v[e]);
-        put4<T>(a.out2, m * a.H + n, v);
+        for (int e = 0; e < 4; ++e) v[e] = silu_t<float>(v[e]);
+        put4(a.out2, m * a.H + n, v);
       }
     }
   } else {
@@ -458,44 +438,43 @@ DEVI void gemm_tile(const GemmArgs& a, const TileAt& tl, char* lds) {
         }
       }
     }
-    return;
-  }
-
-  // epilogue, straight from the accumulators
-  const int m_end = K_::MRAG ? tl.rows : a.M - tl.m0;
+  } else {
+    // epilogue, straight from the accumulators
+    const int m_end = K_::MRAG ? tl.rows : a.M - tl.m0;
 #pragma unroll
-  for (int i = 0; i < MI; ++i) {
-    // (fp32 m/n-contiguous operands: a lane's MI indices are consecutive)
-    const int r = K_::A_KC || !F32 ? (wm * MI + i) * 16 + l16 : (wm * 16 + l16) * MI + i;
-    if (r >= m_end) continue;
-    if constexpr (KIND == GU_FWD) {
+    for (int i = 0; i < MI; ++i) {
+      // (fp32 m/n-contiguous operands: a lane's MI indices are consecutive)
+      const int r = K_::A_KC || !F32 ? (wm * MI + i) * 16 + l16 : (wm * 16 + l16) * MI + i;
+      if (r >= m_end) continue;
+      if constexpr (KIND == GU_FWD) {
 #pragma unroll
-      for (int j = 0; j < NJ / 2; ++j) {
-        const int h = (n0 >> 1) + wn * 8 * NJ + 16 * j + 4 * g4;
-        if (h >= a.H) continue;
-        const size_t m = (size_t)(tl.row0 + r);
-        const f32x4_t G = rounded<T>(acc[i][j]), U = rounded<T>(acc[i][j + NJ / 2]);
-        f32x4_t Hv;
+        for (int j = 0; j < NJ / 2; ++j) {
+          const int h = (n0 >> 1) + wn * 8 * NJ + 16 * j + 4 * g4;
+          if (h >= a.H) continue;
+          const size_t m = (size_t)(tl.row0 + r);
+          const f32x4_t G = acc[i][j], U = acc[i][j + NJ / 2];
+          f32x4_t Hv;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) Hv[e] = silu_t<T>(G[e]) * U[e];
-        put4<T>(a.C, m * 2 * a.H + h, G);
-        put4<T>(a.C, m * 2 * a.H + a.H + h, U);
-        put4<T>(a.out2, m * a.H + h, Hv);
-      }
-    } else {
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        int n;
-        f32x4_t v;
-        if constexpr (K_::B_KC || !F32) {
-          n = n0 + (wn * NJ + j) * 16 + 4 * g4;
-          v = acc[i][j];
-        } else {  // the j-th group of four of the lane's 4 NJ consecutive columns
-          n = n0 + (wn * 16 + 4 * g4) * NJ + 4 * j;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = acc[i][(4 * j + e) % NJ][(4 * j + e) / NJ];
+          for (int e = 0; e < 4; ++e) Hv[e] = silu_t<float>(G[e]) * U[e];
+          put4(a.C, m * 2 * a.H + h, G);
+          put4(a.C, m * 2 * a.H + a.H + h, U);
+          put4(a.out2, m * a.H + h, Hv);
         }
-        if (n < a.N) store_cols<T, KIND>(a, tl, r, n, v);
+      } else {
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          int n;
+          f32x4_t v;
+          if constexpr (K_::B_KC || !F32) {
+            n = n0 + (wn * NJ + j) * 16 + 4 * g4;
+            v = acc[i][j];
+          } else {  // the j-th group of four of the lane's 4 NJ consecutive columns
+            n = n0 + (wn * 16 + 4 * g4) * NJ + 4 * j;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = acc[i][(4 * j + e) % NJ][(4 * j + e) / NJ];
+          }
+          if (n < a.N) store_cols<KIND>(a, tl, r, n, v);
+        }
       }
     }
   }
