@@ -50,7 +50,7 @@ CASES = {
     # the first group does not start at row 0
     "lead-small": ([[63, 64, 0, 129, 144]], 320, [704], "silu", True, 0, "0000"),
     "lead-large": ([LARGE], 2240, [1984], "swiglu", True, 0, "1111"),
-    "lead-k-parts": ([[300, 0, 109]], 192, [2048], "silu", True, 1, "0101"),
+    "lead-k-parts": ([[300, 0, 109]], 192, [2048], "swiglu", True, 1, "0101"),
 }
 LEAD = {"lead-small": 40, "lead-large": 37, "lead-k-parts": 5}  # rows before the first group
 # other kernels that have to run
