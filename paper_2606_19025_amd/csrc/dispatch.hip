@@ -688,11 +688,10 @@ __global__ __launch_bounds__(256) void expert_delta_kernel(DeltaArgs a) {
     // a stream: nothing is read twice, so the accesses are nontemporal
     const f32x4_t s = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(a.start) + i);
     const f32x4_t w = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(a.now) + i);
-    const Peers4 first = load_peers(a.peers, 0, a.n_peers, i);  // with the others in flight
     const f32x4_t dl = s - w;
-    f32x4_t acc = add_peers(first, 0, a.n_peers, dl);
-    for (int p = 4; p < a.n_peers; p += 4)
-      acc = add_peers(load_peers(a.peers, p, a.n_peers, i), p, a.n_peers, acc);
+    f32x4_t acc = dl;
+    for (int p = 0; p < a.n_peers; ++p)
+      acc = acc + __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(a.peers[p]) + i);
     if (a.dl) __builtin_nontemporal_store(dl, reinterpret_cast<f32x4_t*>(a.dl) + i);
     __builtin_nontemporal_store(acc * a.scale, reinterpret_cast<f32x4_t*>(a.avg) + i);
   }
@@ -856,7 +855,7 @@ hipError_t launch_expert_delta(const float* start, const float* now, const float
   a.n_peers = n_peers;
   a.scale = 1.0f / (float)(n_peers + 1);
   if (n == 0) return hipSuccess;
-  MOE_TIMED("expert_delta", s, expert_delta_kernel<<<stream_blocks(n, 12u << 20), 256, 0, s>>>(a));
+  MOE_TIMED("expert_delta", s, expert_delta_kernel<<<peer_stream_blocks(n, n_peers, 4), 256, 0, s>>>(a));
   return hipGetLastError();
 }
 

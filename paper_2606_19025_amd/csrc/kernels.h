@@ -59,34 +59,35 @@ hipError_t launch_ffn_bwd_sets(const moe_ffn_set* sets, int n_sets, int bf16, in
 int num_cus();
 
 // Blocks (256 threads, 16 bytes per access) of an elementwise stream over n fp32
-// elements: two per CU, or one from `one` elements on.  Few blocks read and
-// write few DRAM pages at a time, and the arrays are far larger than the
-// caches: with up to 8192 blocks, 138 M parameters took (us) AdamW 1032, outer
-// step 735 to 762, delta with 3 peers 728; with 256 blocks 757, 608 and 660,
-// with 512 800, 622 and 690.  36 M: AdamW 189 / 195 / 178.  10 M and below: level.
-inline int stream_blocks(size_t n, size_t one) {
+// elements: a vector per thread, up to 8192 blocks, and per_cu blocks per CU from
+// `few` elements on.  Few blocks read and write few DRAM pages at a time, and the
+// arrays are far larger than the caches; but enough loads have to be in flight, and
+// of small arrays the many blocks' are quicker.  Measured (us, nothing in the caches):
+//   256 / 512 / 1024 / 8192 blocks   8 M              25 M                    138 M
+//   AdamW                     52 / 52 / 55 / 49  143 / 136 / 152 / 140  746 / 788 / 865 / 954
+//   outer step                40 / 40 / 42 / 40  114 / 116 / 126 / 119  660 / 667 / 794 / 887
+// Delta and mean add the peers one after another, so a thread has few loads in flight:
+//   512 / 1024 / 4096 / 8192 blocks
+//   delta of 1 peer           33 / 31 / 32 / 32   88 / 88 / 91 / 88    501 / 501 / 586 / 610
+//   delta of 3                50 / 41 / 42 / 43  140 / 115 / 122 / 125 774 / 675 / 751 / 767
+//   delta of 7                84 / 64 / 67 / 66  245 / 183 / 198 / 206 1369 / 1079 / 1137 / 1160
+//   mean of 1                 25 / 20 / 20 / 21   68 / 50 / 51 / 52    359 / 269 / 277 / 283
+//   mean of 3                 43 / 31 / 30 / 30  118 / 82 / 85 / 85    664 / 484 / 474 / 499
+//   mean of 7                 76 / 52 / 51 / 51  222 / 152 / 150 / 155 1249 / 910 / 892 / 892
+// (4 M, mean of 7: 28 us with 1024 blocks, 27 with 8192; 67 M, mean of 15: 862 with
+// 1024, 790 with 4096.  1280 blocks against 1024, 138 M: mean of 3 454 against 483, of 7
+// 852 against 919, delta of 3 684 against 698.  Four peers' loads at once were slower
+// at every number of blocks but the smallest, whose times hang on where the arrays
+// lie: mean of 7, 25 M, 158 to 183, delta of 3, 138 M, 667 to 827 with 256 blocks.)
+inline int stream_blocks(size_t n, size_t few, int per_cu) {
   const size_t want = (n / 4 + 255) / 256;
-  return (int)std::max<size_t>(1, std::min<size_t>(want, (size_t)num_cus() * (n >= one ? 1 : 2)));
+  const size_t most = n < few ? 8192 : (size_t)num_cus() * per_cu;
+  return (int)std::max<size_t>(1, std::min<size_t>(want, most));
 }
-
-// 16-byte vectors i of up to four peers from the p-th on, and their sum onto acc
-// in that order.
-struct Peers4 {
-  f32x4_t q[4];
-};
-DEVI Peers4 load_peers(const float* const* peers, int p, int n_peers, size_t i) {
-  Peers4 r;
-#pragma unroll
-  for (int u = 0; u < 4; ++u)
-    if (p + u < n_peers)
-      r.q[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(peers[p + u]) + i);
-  return r;
-}
-DEVI f32x4_t add_peers(const Peers4& r, int p, int n_peers, f32x4_t acc) {
-#pragma unroll
-  for (int u = 0; u < 4; ++u)
-    if (p + u < n_peers) acc = acc + r.q[u];
-  return acc;
+// AdamW and the outer step; the delta and the mean over peers.
+constexpr size_t kFewBlocks = 16u << 20, kFewBlocksPeers = 8u << 20;
+inline int peer_stream_blocks(size_t n, int n_peers, int per_cu) {
+  return stream_blocks(n, kFewBlocksPeers, n_peers <= 7 ? per_cu : 16);
 }
 
 constexpr int kMaxPeers = 16;

@@ -148,8 +148,8 @@ __global__ __launch_bounds__(256) void replica_mean_kernel(MeanArgs a) {
   const size_t stride = (size_t)gridDim.x * 256;
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += stride) {
     f32x4_t acc = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(a.local) + i);
-    for (int p = 0; p < a.n_peers; p += 4)
-      acc = add_peers(load_peers(a.peers, p, a.n_peers, i), p, a.n_peers, acc);
+    for (int p = 0; p < a.n_peers; ++p)
+      acc = acc + __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(a.peers[p]) + i);
     __builtin_nontemporal_store(acc * a.scale, reinterpret_cast<f32x4_t*>(a.out) + i);
   }
   for (size_t i = n4 * 4 + (size_t)blockIdx.x * 256 + threadIdx.x; i < a.n; i += stride) {
@@ -167,7 +167,7 @@ hipError_t launch_adamw(float* theta, const float* grad, float* m, float* v, siz
   if (n == 0) return hipSuccess;
   AdamArgs a{theta, grad, m, v, static_cast<bf16_t*>(theta_bf16), n, lr, beta1, beta2, eps, wd,
              c1, c2};
-  MOE_TIMED("adamw_step", s, adamw_kernel<<<stream_blocks(n, 64u << 20), 256, 0, s>>>(a));
+  MOE_TIMED("adamw_step", s, adamw_kernel<<<stream_blocks(n, kFewBlocks, n >= (64u << 20) ? 1 : 2), 256, 0, s>>>(a));
   return hipGetLastError();
 }
 
@@ -175,7 +175,7 @@ hipError_t launch_outer_nesterov(float* start, float* now, const float* delta, f
                                  size_t n, float lr, float mu, void* theta_bf16, hipStream_t s) {
   if (n == 0) return hipSuccess;
   OuterArgs a{start, now, delta, mom, static_cast<bf16_t*>(theta_bf16), n, lr, mu};
-  MOE_TIMED("outer_nesterov", s, outer_nesterov_kernel<<<stream_blocks(n, 64u << 20), 256, 0, s>>>(a));
+  MOE_TIMED("outer_nesterov", s, outer_nesterov_kernel<<<stream_blocks(n, kFewBlocks, 1), 256, 0, s>>>(a));
   return hipGetLastError();
 }
 
@@ -189,7 +189,7 @@ hipError_t launch_replica_mean(const float* local, const float* const* peers, in
   a.n = n;
   a.n_peers = n_peers;
   a.scale = 1.0f / (float)(n_peers + 1);
-  MOE_TIMED("replica_mean", s, replica_mean_kernel<<<stream_blocks(n, 12u << 20), 256, 0, s>>>(a));
+  MOE_TIMED("replica_mean", s, replica_mean_kernel<<<peer_stream_blocks(n, n_peers, 5), 256, 0, s>>>(a));
   return hipGetLastError();
 }
 

@@ -139,3 +139,22 @@ def test_adamw_rows_with_own_steps_and_rates(gpu_lib):
         assert np.array_equal(th_d[r].cpu().numpy(), th), r
         assert np.array_equal(m_d[r].cpu().numpy(), m) and np.array_equal(v_d[r].cpu().numpy(), v)
         assert np.array_equal(lp[r].float().cpu().numpy(), rne_bf16(th))
+
+
+@pytest.mark.parametrize("n", [(8 << 20) - 1, (8 << 20) + 3])
+@pytest.mark.parametrize("n_peers", [0, 1, 7, 8])
+def test_peer_streams_around_the_few_blocks_limit(gpu_lib, n, n_peers):
+    """From 8 M elements delta and mean run on few blocks, whose number depends on the
+    peers: the same bits, one rounding per operation, and the element tail."""
+    say(f"[optim] streams n={n} peers={n_peers}")
+    g = torch.Generator(device="cuda").manual_seed(n + n_peers)
+    start, now, *peers = (torch.randn(n, generator=g, device="cuda") for _ in range(2 + n_peers))
+    dl, avg, mean = (torch.full((n,), float("nan"), device="cuda") for _ in range(3))
+    B.moe_expert_delta(start, now, peers, n_peers, n, dl, avg)
+    B.moe_replica_mean(now, peers, n_peers, n, mean)
+    scale = float(np.float32(1.0) / np.float32(n_peers + 1))
+    d, m = start - now, now
+    assert torch.equal(dl, d)
+    for p in peers:
+        d, m = d + p, m + p
+    assert torch.equal(avg, d * scale) and torch.equal(mean, m * scale)
