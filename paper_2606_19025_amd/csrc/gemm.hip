@@ -1318,42 +1318,51 @@ hipError_t reduce_row_parts(const GemmArgs* args, int n_sets, hipStream_t s) {
 // and smaller tiles (two or more blocks per CU) finish earlier.  The choice is by an
 // estimate of the launch's time in each size:
 //   max(longest tile, work / CUs + overlap * longest tile) + bytes / rate
-// with every constant (us per 64-deep k-step and per tile, TB/s) fitted to the
-// launches of 12000 drawn expert blocks (1 to 64 groups of 8 to 3000 rows, d 256 to
-// 4096, H 256 to 2816, with and without shared experts, both expert forms, nothing
-// in the caches); its median error is 4 % for the small tiles and 6 % for the large.
 //
 // The host knows a set's rows only by their bound.  A direct call and a
 // partitioned router fill it, skip-token leaves E_r / E of it, and a size that is
 // right at one end can lose a third at the other: so a size's estimates with all
 // rows present and with 0.4 of them are held against the best of each, and the size
-// whose worse ratio is the smallest is taken.  The small tiles have to win by 5 %:
-// they lose more where the estimate is wrong than they gain where it is close.
-// Over those launches, GU / down projection / dHh + dW_d / dX + dW_gu: the rule takes
-// 0.70 / 0.60 / 0.72 / 0.75 of the time of the large tiles alone (the fastest size of
-// each would take 0.68 / 0.58 / 0.71 / 0.73), and 0.5 / 0.5 / 1.0 / 0.5 % of them over
-// 10 % longer; 1.1 / 0.5 / 2.4 / 1.1 % without the 5 %, 3.4 / 0.8 / 1.1 / 3.8 % by
-// an estimate at 0.6 of the rows alone, without the bytes (200 rows in each of 16
-// groups, d = 2048, H = 1408, forward: 106 us, but 143 by that estimate).
+// whose worse ratio is the smallest is taken.
+//
+// The constants below were fitted to the choices rather than to the times: over 24000
+// launches of drawn expert blocks (1 to 64 groups of 8 to 3000 rows, 0.25 to all of
+// the bound present, even and Zipf-sized, d 256 to 4096, H 256 to 2816, with and
+// without shared experts, both expert forms, caches cold and warm), each timed in
+// every size, they minimise the mean excess over the fastest size, what is lost to
+// the large tiles counted 1.5 times again.  On 16000 others, GU / down projection /
+// dHh + dW_d / dX + dW_gu: the chosen sizes take 2.4 / 1.9 / 1.8 / 1.8 % longer than
+// the fastest of each, 0.69 / 0.58 / 0.70 / 0.72 of the time of the large tiles alone,
+// and are over 10 % slower than they are in 1.9 / 0.6 / 1.3 / 1.1 % of the launches.  (By
+// an estimate at 0.6 of the rows, without bytes: 4.0 / 5.2 / 4.3 / 4.0 % longer, up to
+// 1.8 times the large tiles' time.  Constants fitted to the times, to within 4 to 6 %:
+// 2.9 / 3.5 / 3.4 / 3.7 %.)
 // In us, 256 x 256 / 64 x 128 / 64 x 64 / 32 x 64: GU of 4096 rows in 8 groups, d =
 // 1024, H = 2816: 71 / 101 / 126 / 230, its down projection 48 + 10 (K parts and their
 // sum) / 58 / 64 / 95; up projection of 12004 rows in 12 groups, d = 768, H = 704: 29 /
 // 31 / 36 / 66; 256 rows in 8 groups, d = 1024, H = 2816: GU 33 / 24 / 22 / 30, dX + dW
 // 74 + 9 with K parts, 142 without / 115 / 86; 72 rows in 16 groups and 48 shared, d =
-// 2048, H = 1408 and 2816: down projection 51 + 9 / 47 / 31 / 27.
+// 2048, H = 1408 and 2816: down projection 51 + 9 / 47 / 31 / 27; GU of 200 rows in each
+// of 16 groups, d = 2048, H = 1408: 93 / 107 / 109 / 158.
 struct TileCost {
   TileSize size;
   int bm, bn;
-  double step, lone_step;      // of a CU's time; of a lone block
-  double swiglu, linear, dw;   // per tile: SwiGLU (SiLU) epilogues, others, weight gradients
+  double step, lone_step;      // us per 64-deep k-step: of a CU's time; of a lone block
+  double swiglu, linear, dw;   // us per tile: SwiGLU (SiLU) epilogues, others, weight gradients
   double overlap;
-  double rate, dw_rate;        // operands and rows; fp32 weight gradients
+  double rate, dw_rate;        // TB/s: operands and rows; fp32 weight gradients
 };
 constexpr TileCost kTileCost[] = {
-    {TILE_256x256, 256, 256, 1.27, 1.27, 5.0, 2.0, 5.4, 0.30, 6.0, 9.0},
-    {TILE_64x128, 64, 128, 0.30, 0.82, 1.95, 0.75, 0.4, 0.35, 5.4, 6.5},
-    {TILE_64x64, 64, 64, 0.20, 0.395, 1.45, 0.75, 0.5, 0.33, 5.4, 8.0},
-    {TILE_32x64, 32, 64, 0.16, 0.275, 1.75, 1.2, 0.0, 0.40, 5.6, 8.0}};
+    {TILE_256x256, 256, 256, 0.90, 1.08, 4.8, 4.6, 5.5, 0.125, 13.0, 24.0},
+    {TILE_64x128, 64, 128, 0.327, 0.725, 0.99, 0.36, 0.29, 0.067, 11.3, 8.1},
+    {TILE_64x64, 64, 64, 0.218, 0.328, 0.957, 0.36, 0.50, 0.155, 11.3, 5.25},
+    {TILE_32x64, 32, 64, 0.216, 0.142, 0.938, 0.63, 0.0, 0.211, 11.3, 7.0}};
+
+// (no call to the library's ceil: the choice is made on every launch)
+inline double ceil_pos(double v) {
+  const double whole = (double)(long)v;
+  return whole < v ? whole + 1.0 : whole;
+}
 
 // Estimates (us) of a launch: as it is, and - large tiles of the linear kinds - when
 // its long tiles may be cut into K parts, with their rows' sum launched after it.
@@ -1378,11 +1387,11 @@ Estimate estimate(const TileCost& c, int ka, const GemmArgs* sa, int na, const G
     const int S = mrag || !large ? 1 : split[q - na];
     // groups vary by about the root of their rows
     const double vary = a.n_groups == 1 ? 0.0 : std::sqrt(rows);
-    const double m = mrag ? 0.5 * (std::ceil(std::max(1.0, rows - vary) / c.bm) +
-                                   std::ceil((rows + vary) / c.bm))
+    const double m = mrag ? 0.5 * (ceil_pos(std::max(1.0, rows - vary) / c.bm) +
+                                   ceil_pos((rows + vary) / c.bm))
                           : (double)ceil_div(a.M, c.bm) * S;
     const double tiles = m * a.n_groups * ceil_div(a.N, c.bn);
-    const double steps = std::max(1.0, std::ceil((mrag ? a.K : rows / S) / 64.0));
+    const double steps = std::max(1.0, ceil_pos((mrag ? a.K : rows / S) / 64.0));
     const double tile = !mrag ? c.dw : linear ? c.linear : c.swiglu;
     work += tiles * (steps * c.step + tile);
     steps_sum += tiles * steps;
@@ -1396,10 +1405,10 @@ Estimate estimate(const TileCost& c, int ka, const GemmArgs* sa, int na, const G
   const double per_cu = work / num_cus();
   const double longest = std::max(long_m, long_k);
   double t = std::max(longest, per_cu + c.overlap * longest);
-  if (large && nb > 0) t = std::max(per_cu + c.overlap * longest, 0.9 * long_m + 0.6 * long_k);
+  if (large && nb > 0) t = std::max(per_cu + c.overlap * longest, 1.12 * long_m + 0.81 * long_k);
   // one block per CU: whole rounds of tiles
   if (large && nb == 0 && tiles_sum > 0)
-    t = std::max(longest, std::ceil(tiles_sum / num_cus()) * work / tiles_sum);
+    t = std::max(longest, ceil_pos(tiles_sum / num_cus()) * work / tiles_sum);
   const double mem = bytes / c.rate * 1e-6, dw_mem = dw_bytes / c.dw_rate * 1e-6;
   Estimate e{t + mem + dw_mem, INFINITY};
   if (!large || !linear) return e;
@@ -1409,13 +1418,13 @@ Estimate estimate(const TileCost& c, int ka, const GemmArgs* sa, int na, const G
     const GemmArgs& a = sa[q];
     if (a.n_groups == 0 || a.cap == 0) continue;
     const double S = std::min((double)row_parts_max(1, a.cap, a.N),
-                              std::ceil(std::ceil(a.K / 64.0) / (4.0 / 3.0 * steps_sum / num_cus())));
+                              ceil_pos(ceil_pos(a.K / 64.0) / (4.0 / 3.0 * steps_sum / num_cus())));
     if (S > 1) part_bytes += 8.0 * S * rows_of(a) * a.n_groups * a.N;
   }
-  if (part_bytes == 0) e.parts = e.us + 5.0;  // the sum's launch, which finds one part
+  if (part_bytes == 0) e.parts = e.us + 5.4;  // the sum's launch, which finds one part
   else
-    e.parts = (nb > 0 ? 0.85 * long_k + 0.73 * per_cu + 2.0 * dw_mem : 2.0 * per_cu) + 0.35 * mem +
-              0.9 * part_bytes / 5.0 * 1e-6 + 9.0;
+    e.parts = (nb > 0 ? 0.95 * long_k + 0.75 * per_cu + 2.7 * dw_mem : 4.75 * per_cu) + 0.19 * mem +
+              part_bytes / 3.0e6 + 15.6;
   return e;
 }
 
@@ -1434,7 +1443,7 @@ TileSize choose_tiles(int ka, const GemmArgs* sa, int na, const GemmArgs* sb, in
       us[i][p] = INFINITY;
       if (kTileCost[i].size == TILE_32x64 && nb > 0) continue;
       const Estimate e = estimate(kTileCost[i], ka, sa, na, sb, nb, kPresent[p], split);
-      us[i][p] = (e.us + 4.0) * (i == 0 ? 1.0 : 1.05);  // 4: the launch itself
+      us[i][p] = e.us + 4.0;  // 4: the launch itself
       if (i == 0 && may) us[kSizes][p] = e.parts + 4.0;
     }
     for (int i = 0; i < kCand; ++i) best[p] = std::min(best[p], us[i][p]);

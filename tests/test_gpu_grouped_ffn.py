@@ -7,9 +7,8 @@ one below, at and above 128 and 256 rows; hidden and model widths that leave a
 partial column tile; K extents (d, H, 2H) of one to several k-steps and ragged
 token counts for the weight-gradient kinds; the backward both without a workspace
 and with one.  Both expert forms.  Which tiles a launch takes is the library's
-choice: most of these take the small ones; the single large group's backward
-takes the large ones with its rows cut into parts, and few-tiles-long-k's dX cuts
-its reduction.  test_gpu_gemm_tiles names the kernels that each of its shapes runs.
+choice, for most of these the small ones; test_gpu_gemm_tiles names the kernels
+that each of its shapes runs.
 
 Every output is compared with the oracle (Sec. 3.2 expert FFN per resident
 expert, App. B.3.1 for the SiLU form) at the bf16 tolerance, normwise.
