@@ -1422,9 +1422,10 @@ Estimate estimate(const TileCost& c, int ka, const GemmArgs* sa, int na, const G
     if (S > 1) part_bytes += 8.0 * S * rows_of(a) * a.n_groups * a.N;
   }
   if (part_bytes == 0) e.parts = e.us + 5.4;  // the sum's launch, which finds one part
-  else
-    e.parts = (nb > 0 ? 0.95 * long_k + 0.75 * per_cu + 2.7 * dw_mem : 4.75 * per_cu) + 0.19 * mem +
-              part_bytes / 3.0e6 + 15.6;
+  else if (nb > 0)
+    e.parts = 0.95 * long_k + 0.75 * per_cu + 2.7 * dw_mem + 0.19 * mem + part_bytes / 3.0e6 + 15.6;
+  else  // (about one launch of 500, where it gains up to a quarter)
+    e.parts = 1.34 * per_cu + 0.78 * mem + part_bytes / 4.8e6 + 17.7;
   return e;
 }
 

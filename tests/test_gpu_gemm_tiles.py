@@ -47,6 +47,8 @@ CASES = {
     # few tiles with a long reduction: dX in K parts
     "k-parts": ([[300, 0, 109]], 192, [3328], "swiglu", True, 0, "0001"),
     "k-parts-shared": ([[100, 0, 270, 10], [132]], 256, [2432, 4864], "swiglu", True, 1, "0001"),
+    # the down projection too
+    "k-parts-down": ([[60, 0, 30, 9], [962]], 512, [4224, 8448], "silu", True, 0, "1110"),
     # the first group does not start at row 0
     "lead-small": ([[63, 64, 0, 129, 144]], 320, [704], "silu", True, 0, "0000"),
     "lead-large": ([LARGE], 2240, [1984], "swiglu", True, 0, "1111"),
@@ -56,7 +58,7 @@ LEAD = {"lead-small": 40, "lead-large": 37, "lead-k-parts": 5}  # rows before th
 # other kernels that have to run
 ALSO = {"one-group-split": "splitk_reduce", "one-group-split-silu-acc": "splitk_reduce",
         "k-parts": "splitk_rows_reduce", "k-parts-shared": "splitk_rows_reduce",
-        "lead-k-parts": "splitk_rows_reduce"}
+        "k-parts-down": "splitk_rows_reduce", "lead-k-parts": "splitk_rows_reduce"}
 
 
 @pytest.mark.parametrize("name", sorted(CASES))
