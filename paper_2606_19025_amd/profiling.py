@@ -46,10 +46,9 @@ def _gemm_launch_name(ka: int, kb: int) -> str:
     return GEMM_KINDS[ka] if ka == kb else _MERGED.get((ka, kb), "gemm_merged")
 
 
-def _garbled_launch_name(kb: int) -> str:
-    """Of a launch whose first kind the profiler's demangler lost: no launch has a
-    weight gradient (4, 5) alone."""
-    return {4: "gemm_merged", 5: "gemm_dx_dwgu"}.get(kb, GEMM_KINDS[kb])
+def _launch_of_first_kind(ka: int) -> str:
+    """Each first kind has one launch: alone, or merged with its second kind."""
+    return next((n for (a, _), n in _MERGED.items() if a == ka), GEMM_KINDS[ka])
 
 
 # kernel symbol (demangled, as rocprofv3 prints it) -> timing name
@@ -58,9 +57,10 @@ _SYMBOLS = [
     (r"gemm_bf16_kernel(?:<|ILi)(\d)", lambda m: GEMM_KINDS[int(m.group(1))]),
     (r"gemm_tile_kernel(?:<(?:[a-z_0-9]+, )?|I(?:f|DF16b)Li)(\d)(?:, |ELi)(\d)",
      lambda m: _gemm_launch_name(int(m.group(1)), int(m.group(2))) + "_tile"),
-    # bf16 template arguments come out of rocprofv3 as <bool _Accum, int, E, KB, ...>
-    (r"gemm_tile_kernel<bool _Accum, int, E, (\d)",
-     lambda m: _garbled_launch_name(int(m.group(1))) + "_tile"),
+    # <bf16, KA, KB, ...>: rocprofv3's demangler takes DF16b for a bool and the KA of Li{KA}E
+    # for the length of a name: <bool _Accum, int, E, 1, ...>, <bool _Accum, int, ELi, ELi2E, ...>
+    (r"gemm_tile_kernel<bool _Accum, int, (\w+),",
+     lambda m: _launch_of_first_kind(len(m.group(1))) + "_tile"),
     (r"route_fwd_kernel", lambda m: "route_fwd"),
     (r"route_dz_kernel", lambda m: "route_dz"),
     (r"route_bwd_mfma_kernel", lambda m: "route_bwd_mfma"),

@@ -85,9 +85,9 @@ def test_symbols_of_a_trace_have_timing_names():
     assert len(ours) > 50
     for s in ours:
         assert P.timing_name(s) is not None, s
-    garbled = "void moe::(anonymous namespace)::gemm_tile_kernel<bool _Accum, int, E, {}, 2, 4, 2>(x)"
-    assert P.timing_name(garbled.format(1)) == "gemm_down_fwd_tile"
-    assert P.timing_name(garbled.format(5)) == "gemm_dx_dwgu_tile"
+    garbled = "void moe::(anonymous namespace)::gemm_tile_kernel<bool _Accum, int, {}, 4, 2>(x)"
+    assert P.timing_name(garbled.format("E, 1, 2")) == "gemm_down_fwd_tile"
+    assert P.timing_name(garbled.format("ELi, ELi2E")) == "gemm_dx_dwgu_tile"
     assert P.timing_name("_ZN3moe12_GLOBAL__N_116gemm_tile_kernelIDF16bLi7ELi4ELi2ELi4ELi2EEEvNS_10GemmLaunchE") \
         == "gemm_dh_dwd_tile"
 
